@@ -51,6 +51,9 @@ hipError_t launch_skinny(const Segments& seg, const GemmArgs& a, bool gated, hip
 bool skinny_ok(const GemmArgs& a);
 constexpr int kChunkRows = kChunkRowsHost;
 constexpr int kBlockElems = 512;  // one 1 KB block of the chunk-blocked layout
+// The mid-sized kernel: seg with device offsets, sh (nullable) with static
+// rows in the same launch; the caller has checked both (tiled_ok).
+hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st);
 hipError_t launch_tiled(const Segments& seg, const GemmArgs& a, bool gated, hipStream_t st);
 
 // Largest per-group row count routed to the weight-streaming kernel.

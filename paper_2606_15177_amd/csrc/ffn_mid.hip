@@ -1,0 +1,387 @@
+// Expert FFN for mid-sized batches: more rows per expert than one decode
+// step has, far fewer than fill 256-row tiles (chunked prefill, decode of
+// hundreds of tokens over many experts).  What bounds it is reading the
+// active experts' weights once; hot and shared experts add MFMA work.
+//
+// Items.  One workgroup of four waves takes one item: up to 128 token rows of
+// one group (a chunk) times a block of weight rows.  Groups of up to 64 rows
+// take narrow items of 128 weight rows, larger groups wide ones of 256 (of
+// 128 where a launch has few wide items, which would otherwise run on long
+// after the rest: Mixtral down at 100 tokens 318 -> 223 us, DSV2-Lite down at
+// 200 tokens 97 -> 71 us).  A wave owns 32-row blocks of the weights (gate/up:
+// 16 gate rows and the 16 up rows of the same columns, which the MFMA's C
+// layout puts into one lane) and all token rows of the chunk.  Dispatched as
+// plain workgroups, two per CU: a persistent grid over 256-row tiles left CUs
+// idle in its last round and one workgroup per CU waiting at its barriers.
+//
+// Pipeline.  Weights and token rows go by buffer_load_dwordx4 ... lds straight
+// into a ring of K stages in 80 KB of LDS, D - 1 stages ahead; each wave loads
+// its own weights and a quarter of the chunk's token rows; one barrier per
+// stage.  Narrow items: 64-wide stages, four (<= 32 rows) or three in the
+// ring, 96 and 64 KB of weights in flight per CU.  Wide items: 32-wide stages,
+// so that three of 24 KB fit.  Splitting K over the waves as the decode kernel
+// does was slower at every size here (Qwen3 down at 256 tokens 77 us against
+// 90 and 141 with 2 and 4 parts: each part needs token rows of its own), and
+// so were 64-row chunks for hot experts (DSV2-Lite layer, 4096 tokens: 971
+// against 825 us).
+//
+// Order.  Items are numbered per kind; each XCD (workgroup id mod 8) owns a
+// contiguous run of every kind, so an expert's token rows, and the weight
+// block that its chunks share, stay in one L2 (DSV2-Lite gate/up at 1021
+// tokens fetches 0.95 GB instead of 1.09).  Within an XCD the wide (MFMA
+// bound) and narrow (HBM bound) items take turns.  The dispatcher deals
+// workgroups to the shader engines strictly in turn, and waits for the engine
+// whose turn it is: turns of one item put all wide ones on the same two
+// engines of an XCD and left the others idle half the time.  Turns of kTurn
+// items give every engine both (Qwen3 layer at 800 tokens 316 -> 286 us,
+// DSV2-Lite at 1021 tokens 448 -> 342 us).
+//
+// Measured (layer, 256-row tiles -> this kernel): Qwen3, 256 tokens 288 -> 244
+// us (gate/up streams 5.6 TB/s); DSV2-Lite, 400 tokens 341 -> 266 us; the
+// DSV3 share, 256 tokens 544 -> 430 us; Mixtral, 65 tokens 607 -> 525 us.
+#include "ffn_impl.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace moe {
+namespace {
+
+constexpr int kMidRows = 128;        // token rows of a chunk
+constexpr int kWideRows = 64;        // groups of more rows take wide items
+constexpr int kMidCols = 128;        // weight rows of a narrow item
+constexpr int kFewWide = 128;        // fewer wide items than this take 128 weight rows: half the CUs' worth
+constexpr int kMidThreads = 4 * kWave;
+constexpr int kMidLds = 80 * 1024;   // two workgroups per CU
+constexpr int kXcds = 8;
+constexpr int kTurn = 8;             // items per turn: a multiple of an XCD's shader engines
+constexpr uint32_t kDead = 0x80000000u;  // past the descriptor's range: reads zeros, no traffic
+
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+__device__ __forceinline__ void stage_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+}
+
+struct MidArgs {
+  GemmArgs g;   // the routed experts (device offsets)
+  GemmArgs sp;  // static rows (shared experts); sp.static_rows == 0: none
+};
+
+// first of n items that XCD x owns (x = kXcds: n)
+__device__ __forceinline__ int run_start(int n, int x) {
+  return static_cast<int>(static_cast<long long>(n) * x / kXcds);
+}
+
+// column blocks of a group of n rows: narrow items cover `cols` output columns, wide ones wide_cols
+__device__ __forceinline__ int col_blocks(int n, int N, int cols, int wide_cols) {
+  return ceil_div(N, n > kWideRows ? wide_cols : cols);
+}
+
+template <bool GATED>
+__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mid_kernel(MidArgs ma) {
+  constexpr int OUT_COLS = GATED ? kMidCols / 2 : kMidCols;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+
+  // ---- which item ----
+  // Items are numbered per kind (shared, wide, narrow) by group, column block
+  // and chunk (fastest); an XCD owns an equal, contiguous run of each kind.
+  const int sp_m = ma.sp.static_rows;
+  const int sp_chunks = sp_m > 0 ? ceil_div(sp_m, kMidRows) : 0;
+  int n_wide = 0, n_narrow = 0;  // items of the routed groups
+  for (int gg = lane; gg < ma.g.groups; gg += kWave) {
+    const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
+    const int it = ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, 2 * OUT_COLS);
+    n_wide += n > kWideRows ? it : 0;
+    n_narrow += n > kWideRows ? 0 : it;
+  }
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    n_wide += __shfl_xor(n_wide, off);
+    n_narrow += __shfl_xor(n_narrow, off);
+  }
+  n_wide = __builtin_amdgcn_readfirstlane(n_wide);
+  n_narrow = __builtin_amdgcn_readfirstlane(n_narrow);
+  int n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, 2 * OUT_COLS) : 0;
+  int wide_cols = 2 * OUT_COLS;
+  if (n_shared + n_wide < kFewWide) {
+    wide_cols = OUT_COLS;
+    n_shared = sp_m > 0 ? sp_chunks * ceil_div(ma.sp.N, OUT_COLS) : 0;
+    n_wide = 0;
+    for (int gg = lane; gg < ma.g.groups; gg += kWave) {
+      const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
+      n_wide += n > kWideRows ? ceil_div(n, kMidRows) * ceil_div(ma.g.N, OUT_COLS) : 0;
+    }
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) n_wide += __shfl_xor(n_wide, off);
+    n_wide = __builtin_amdgcn_readfirstlane(n_wide);
+  }
+  const int xcd = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+  const int s_lo = run_start(n_shared, xcd), w_lo = run_start(n_wide, xcd), n_lo = run_start(n_narrow, xcd);
+  const int my_shared = run_start(n_shared, xcd + 1) - s_lo;
+  const int my_heavy = my_shared + run_start(n_wide, xcd + 1) - w_lo;
+  const int my_narrow = run_start(n_narrow, xcd + 1) - n_lo;
+  if (i >= my_heavy + my_narrow) return;
+  // heavy (shared and wide) and narrow items take turns while there are both
+  const int turns = min(my_heavy, my_narrow) / kTurn;
+  bool narrow;
+  int idx;
+  if (i < 2 * turns * kTurn) {
+    narrow = (i / kTurn) & 1;
+    idx = i / (2 * kTurn) * kTurn + i % kTurn;
+  } else {
+    idx = i - turns * kTurn;
+    narrow = idx >= my_heavy;
+    idx = narrow ? i - my_heavy : idx;
+  }
+  const bool shared = !narrow && idx < my_shared;
+  const bool wide = shared ? sp_m > kWideRows : !narrow;
+  idx = narrow ? n_lo + idx : shared ? s_lo + idx : w_lo + idx - my_shared;
+  int g = 0, row_base = 0, m = sp_m, item = idx;
+  if (!shared) {
+    for (int g0 = 0;; g0 += kWave) {
+      const int gg = g0 + lane;
+      const int o0 = gg < ma.g.groups ? ma.g.offsets[gg] : 0;
+      const int n = gg < ma.g.groups ? ma.g.offsets[gg + 1] - o0 : 0;
+      const int own = (n > kWideRows) == wide ? ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, wide_cols) : 0;
+      int inc = own;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+      }
+      const uint64_t past = __ballot(inc > idx);
+      if (past) {
+        const int l = __ffsll(static_cast<long long>(past)) - 1;
+        g = g0 + l;
+        row_base = __builtin_amdgcn_readlane(o0, l);
+        m = __builtin_amdgcn_readlane(n, l);
+        item = idx - __builtin_amdgcn_readlane(inc - own, l);
+        break;
+      }
+      if (g0 + kWave >= ma.g.groups) return;  // not reached: idx lies within the groups' items
+      idx -= __builtin_amdgcn_readlane(inc, kWave - 1);
+    }
+  }
+  const int n_chunks = ceil_div(m, kMidRows);
+  int nblk = item / n_chunks;
+  int chunk = item - nblk * n_chunks;
+  g = __builtin_amdgcn_readfirstlane(g);
+  row_base = __builtin_amdgcn_readfirstlane(row_base);
+  m = __builtin_amdgcn_readfirstlane(m);
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
+  nblk = __builtin_amdgcn_readfirstlane(nblk);
+
+  const int K = shared ? ma.sp.K : ma.g.K;
+  const int N = shared ? ma.sp.N : ma.g.N;
+  const int ldw = shared ? ma.sp.ldw : ma.g.ldw;
+  const int kseg = shared ? ma.sp.kseg : ma.g.kseg;
+  const size_t seg_stride = shared ? ma.sp.seg_stride : ma.g.seg_stride;
+  const int32_t* x_rows = shared ? nullptr : ma.g.x_rows;
+  // the group's rows in equal chunks of whole 32-row MFMA tiles
+  const int chunk_rows = ceil_div(ceil_div(m, ceil_div(m, kMidRows)), 32) * 32;
+  const int m0 = chunk * chunk_rows;
+  const int rows = min(chunk_rows, m - m0);
+  const int n0 = nblk * (wide ? wide_cols : OUT_COLS);
+
+  // ---- loads ----
+  const size_t gofs = (shared ? size_t{0} : static_cast<size_t>(g) * ma.g.group_stride) + static_cast<size_t>(n0) * ldw;
+  const uint16_t* w0 = (shared ? ma.sp.w0 : ma.g.w0) + gofs;
+  const uint16_t* w1 = GATED ? (shared ? ma.sp.w1 : ma.g.w1) + gofs : w0;
+  const uint16_t* xb = shared ? ma.sp.x : ma.g.x;
+  if (x_rows == nullptr) xb += static_cast<size_t>(row_base + m0) * K;
+  const __amdgpu_buffer_rsrc_t rs_w0 =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(w0), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_w1 =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(w1), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_x =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(xb), 0, 0x7fffffff, 0x00020000);
+  const bool segmented = kseg < K;
+  const int lrow = lane & 31, lhalf = lane >> 5;
+
+  auto body = [&](auto nsub_c, auto wb_c, auto bk_c, auto depth_c) {
+    constexpr int NSUB = decltype(nsub_c)::value;
+    constexpr int WB = decltype(wb_c)::value;
+    constexpr int BK = decltype(bk_c)::value;
+    constexpr int D = decltype(depth_c)::value;
+    constexpr int ROW = BK * 2;              // bytes of an LDS row
+    constexpr int CPR = ROW / 16;            // 16-byte chunks per row
+    constexpr int RPI = kWave / CPR;         // rows per load instruction
+    constexpr int SWZ = 16 / CPR;            // rows sharing one swizzle key
+    constexpr int XPART = NSUB * 32 * ROW;   // token rows of one K part
+    constexpr int STAGE = XPART + WB * 4 * 32 * ROW;
+    constexpr int XL = NSUB * 32 / RPI / 4; // token loads per wave and stage
+    constexpr int WL = WB * 32 / RPI;           // weight loads per wave and stage
+    constexpr int LOADS = XL + WL;
+    constexpr int KS = BK / 16;              // MFMA K-steps per stage
+    static_assert(D * STAGE <= kMidLds && XL * RPI * 4 == NSUB * 32, "the ring fits, whole loads fill the token rows");
+    const int lr = lane / CPR;               // row of a load
+    // 16-byte chunk c of LDS row r sits at slot c ^ ((r / SWZ) % CPR); load i
+    // of the weights fills the wave's rows RPI i .., load q of the tokens the
+    // rows RPI (4 q + wave) ..
+    uint32_t woff[WL], xoff[XL];
+    int wpiece[WL], xpiece[XL];
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int r = RPI * i + lr;
+      const int b = WB * wave + r / 32;  // 32-row block of weights
+      const int col = GATED ? 16 * b + (r & 15) : 32 * b + r % 32;
+      woff[i] = n0 + col < N ? static_cast<uint32_t>(col * ldw * 2) : kDead;
+      wpiece[i] = (lane % CPR) ^ ((r / SWZ) % CPR);
+    }
+#pragma unroll
+    for (int q = 0; q < XL; ++q) {
+      const int r = RPI * (4 * q + wave) + lr;
+      int src = r;
+      if (x_rows) src = x_rows[row_base + m0 + min(r, rows - 1)];
+      xoff[q] = r < rows ? static_cast<uint32_t>(src * K * 2) : kDead;
+      xpiece[q] = (lane % CPR) ^ ((r / SWZ) % CPR);
+    }
+    const int nst = ceil_div(K, BK);
+    int s_ld = 0, slot_ld = 0;  // next stage to load and its slot
+    int kb_ld = static_cast<int>((static_cast<unsigned>(nblk) * 7u + static_cast<unsigned>(g) * 3u) % static_cast<unsigned>(nst));
+    auto issue = [&]() {
+      unsigned char* st = smem + slot_ld * STAGE;
+      const int k0 = kb_ld * BK;
+      const uint32_t dead = s_ld < nst ? 0u : kDead;
+#pragma unroll
+      for (int q = 0; q < XL; ++q) {
+        const int k = k0 + xpiece[q] * 8;
+        const uint32_t kill = dead | (k < K ? 0u : kDead) | (xoff[q] & kDead);
+        load_lds16(rs_x, st + RPI * (4 * q + wave) * ROW, (xoff[q] + static_cast<uint32_t>(k * 2)) | kill);
+      }
+      unsigned char* wl = st + XPART + wave * (WB * 32 * ROW);
+#pragma unroll
+      for (int i = 0; i < WL; ++i) {
+        const int k = k0 + wpiece[i] * 8;
+        const uint32_t kill = dead | (k < K ? 0u : kDead) | (woff[i] & kDead);
+        uint32_t col = static_cast<uint32_t>(k * 2);
+        if (segmented) {
+          const int kc = k < K ? k : 0;
+          const int q = kc / kseg;
+          col = static_cast<uint32_t>((static_cast<size_t>(q) * seg_stride + (kc - q * kseg)) * 2);
+        }
+        load_lds16(GATED && ((RPI * i) & 16) ? rs_w1 : rs_w0, wl + i * 1024, (woff[i] + col) | kill);
+      }
+      ++s_ld;
+      if (++slot_ld == D) slot_ld = 0;
+      if (++kb_ld == nst) kb_ld = 0;
+    };
+    f32x16 acc[WB][NSUB];
+#pragma unroll
+    for (int b = 0; b < WB; ++b)
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) acc[b][s] = f32x16{};
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s) issue();
+    int slot = 0;
+    for (int j = 0; j < nst; ++j) {
+      __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * LOADS));  // own loads of stage j landed
+      stage_barrier();  // everyone's have, and everyone has read stage j - 1
+      issue();          // stage j + D - 1 into the slot of stage j - 1
+      const unsigned char* xp = smem + slot * STAGE;
+      const unsigned char* wp = smem + slot * STAGE + XPART + wave * (WB * 32 * ROW);
+      bf16x8 wf[KS][WB], xf[KS][NSUB];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int cs = ((2 * ks + lhalf) ^ ((lrow / SWZ) % CPR)) << 4;
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+          wf[ks][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wp + (32 * b + lrow) * ROW + cs));
+#pragma unroll
+        for (int s = 0; s < NSUB; ++s)
+          xf[ks][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(xp + (32 * s + lrow) * ROW + cs));
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s) acc[b][s] = mfma32x32x16(wf[ks][b], xf[ks][s], acc[b][s]);
+      if (++slot == D) slot = 0;
+    }
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));  // the loads past the last stage: nothing may still write the LDS
+    // ---- epilogue: lane holds C[n = 8 v4 + 4 lhalf + i][t = lrow] ----
+    uint16_t* out = (shared ? ma.sp.out : ma.g.out) + static_cast<size_t>(row_base + m0) * N;
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) {
+      const int r = 32 * s + lrow;
+      constexpr int PAIRS = GATED ? 1 : 2;  // pairs of 8-column groups the wave writes
+#pragma unroll
+      for (int bp = 0; bp < WB * PAIRS; ++bp) {
+        const int b = bp / PAIRS, p = bp % PAIRS;
+        uint32_t pk[2][2];
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          float o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float c0 = acc[b][s][4 * (2 * p + v) + i];
+            if constexpr (GATED)
+              o[i] = silu(c0) * acc[b][s][4 * (2 + v) + i];
+            else
+              o[i] = c0;
+          }
+          pk[v][0] = cvt_pk_bf16(o[0], o[1]);
+          pk[v][1] = cvt_pk_bf16(o[2], o[3]);
+        }
+        // lower lanes take columns 0..7, upper lanes 8..15 of the pair
+        const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
+        const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
+        const int col = n0 + (GATED ? 16 * (WB * wave + b) : 32 * (WB * wave + b) + 16 * p) + 8 * lhalf;
+        if (r < rows && col < N) store16(out + static_cast<size_t>(r) * N + col, v);
+      }
+    }
+  };
+  using std::integral_constant;
+  using C1 = integral_constant<int, 1>;
+  using C2 = integral_constant<int, 2>;
+  using C3 = integral_constant<int, 3>;
+  using C4 = integral_constant<int, 4>;
+  using C5 = integral_constant<int, 5>;
+  using K32 = integral_constant<int, 32>;
+  using K64 = integral_constant<int, 64>;
+  if (wide && wide_cols > OUT_COLS)
+    body(C4{}, C2{}, K32{}, C3{});
+  else if (wide)
+    body(C4{}, C1{}, K32{}, C5{});
+  else if (rows > 32)
+    body(C2{}, C1{}, K64{}, C3{});
+  else
+    body(C1{}, C1{}, K64{}, C4{});
+}
+
+template <bool GATED>
+hipError_t launch_mid_t(const Segments& seg, const GemmArgs& g, const GemmArgs& sp, hipStream_t st) {
+  constexpr int OUT_COLS = GATED ? kMidCols / 2 : kMidCols;
+  static unsigned long long lds_set = 0;  // devices with the LDS limit raised
+  const hipError_t e = set_max_dynamic_lds(reinterpret_cast<const void*>(&mid_kernel<GATED>), kMidLds, &lds_set);
+  if (e != hipSuccess) return e;
+  // at most one partly filled chunk per group; wide items need fewer column blocks
+  const long long chunks = seg.total_rows / kMidRows + std::min(seg.groups, seg.total_rows);
+  long long items = chunks * ceil_div(g.N, OUT_COLS);
+  if (sp.static_rows > 0) items += static_cast<long long>(ceil_div(sp.static_rows, kMidRows)) * ceil_div(sp.N, OUT_COLS);
+  const long long per_xcd = items / kXcds + 3;  // each kind's run rounds up by one
+  if (items == 0) return hipSuccess;
+  hipLaunchKernelGGL((mid_kernel<GATED>), dim3(static_cast<unsigned>(per_xcd * kXcds)), dim3(kMidThreads), kMidLds,
+                     st, MidArgs{g, sp});
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st) {
+  const GemmArgs none{};
+  return gated ? launch_mid_t<true>(seg, a, sh ? *sh : none, st) : launch_mid_t<false>(seg, a, sh ? *sh : none, st);
+}
+
+}  // namespace moe

@@ -72,6 +72,19 @@ constexpr int kBM = 256;             // token rows per tile
 constexpr int kBN = 256;             // weight rows per tile
 constexpr int kThreads = 8 * kWave;  // eight waves, two per SIMD
 constexpr int kMaxGroups = 1024;
+// Mean rows per routed expert (T k / E) up to which a grouped GEMM takes the
+// mid-sized kernel.  Time of the 256-row tiles over that kernel's, by GEMM
+// (kernel trace):
+//   long K or no shared rows (kMidMean): DSV3 share gate/up 1.14 at a mean of
+//     16, 1.01 at 28, 1.00 at 38; Mixtral gate/up 1.02 at 32, 0.97 at 50;
+//     Mixtral down 1.01 at 32, 0.93 at 75; Qwen3 down 1.01 at 50, 0.87 at 94;
+//   gate/up with K < kHalfTailK (kMidMeanUp): DSV2-Lite 1.20 at 66, 1.10 at
+//     141, 0.89 at 206; Qwen3 1.13 at 50, 1.05 at 156, 0.95 at 188;
+//   down with shared rows in the launch (kMidMeanShared; whole 256-row tiles
+//     otherwise), by the mean over all weight rows, shared ones included:
+//     DSV2-Lite 1.64 at 85, 1.16 at 303, 0.97 at 363; DSV3 share 1.21 at 91,
+//     1.04 at 212, 0.96 at 303.
+constexpr int kMidMean = 40, kMidMeanUp = 160, kMidMeanShared = 256;
 constexpr int kHalfTailK = 4096;  // K from which grouped launches take half tail tiles
 constexpr int kBlockM = 8;           // m-tiles per block of a static group's tile order
 
@@ -1164,6 +1177,25 @@ bool gemm_ok(const Segments& seg, const GemmArgs& a) {
   return ffn_streams_weights(seg) ? skinny_ok(a) : tiled_ok(seg, a);
 }
 
+// Whether a grouped problem past the weight-streaming sizes takes the
+// mid-sized kernel (ffn_mid.hip) rather than 256-row tiles; `sh` joins it.
+bool takes_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+  if (a.static_rows > 0 || (sh && sh->static_rows == 0)) return false;
+  if (seg.mean_rows <= kMidMean) return true;
+  if (!gated && sh) {
+    const long long wr = static_cast<long long>(seg.groups) * a.K;
+    return (seg.mean_rows * wr + static_cast<long long>(sh->static_rows) * sh->K) <= kMidMeanShared * (wr + sh->K);
+  }
+  if (a.K >= kHalfTailK) return false;
+  if (gated && seg.mean_rows <= kMidMeanUp) return true;
+  // few tiles: 256-row tiles would leave a third of the CUs without one
+  // (16 experts, 3000 tokens, H 1024, I 512: layer 71.3 -> 55.9 us; with 216
+  // tiles, H 2304, I 1536 down, the tiles are faster: layer 169 against 182)
+  const long long tiles = static_cast<long long>(seg.groups) * ceil_div(std::max(seg.mean_rows, 1), kBM) *
+                          ceil_div(a.N, gated ? kBN / 2 : kBN);
+  return 3 * tiles < 2 * device_cu_count();
+}
+
 // One GEMM on its kernel, or two in one tiled launch when both take the
 // tiled kernel, the second has static rows and on its own it would leave a
 // partly filled last round of tiles: the routed tiles then fill it.  (When
@@ -1172,6 +1204,10 @@ bool gemm_ok(const Segments& seg, const GemmArgs& a) {
 hipError_t launch_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh,
                         bool gated, hipStream_t st) {
   const bool tiled = !ffn_streams_weights(seg);
+  if (tiled && takes_mid(seg, a, sh, gated)) {
+    if (!tiled_ok(seg, a) || (sh && !tiled_ok(*sh_seg, *sh))) return hipErrorInvalidValue;
+    return launch_mid(seg, a, sh, gated, st);
+  }
   const int out_cols = gated ? kBN / 2 : kBN;
   const bool merge = sh != nullptr && tiled && !ffn_streams_weights(*sh_seg) && sh_seg->offsets == nullptr &&
                      static_cast<long long>(ceil_div(sh_seg->static_rows, kBM)) * ceil_div(sh->N, out_cols) %

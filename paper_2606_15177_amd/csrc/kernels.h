@@ -71,13 +71,16 @@ hipError_t launch_gather_rows(int capacity, int H, const int32_t* perm_token,
 // A grouped GEMM over row segments.  Group g owns rows [offsets[g],
 // offsets[g+1]) of the activation matrix (or rows [0, static_rows) of a single
 // group when offsets == nullptr).  max_rows bounds the rows of any one group
-// and total_rows the rows of all groups (both host-side capacities).
+// and total_rows the rows of all groups (both host-side capacities);
+// mean_rows is what a group holds on average when routing is even (a choice
+// of kernel only: any distribution is correct).
 struct Segments {
   const int32_t* offsets;
   int groups;
   int static_rows;
   int max_rows;
   int total_rows;
+  int mean_rows;
 };
 
 // h[r][i] = silu(sum_c X[r][c] Wg[g][i][c]) * (sum_c X[r][c] Wu[g][i][c]),

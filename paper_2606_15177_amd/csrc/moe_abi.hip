@@ -57,7 +57,7 @@ int64_t sh_width(const moe_dims* d) {
 
 // Decode-sized batches run the routed GEMMs on chunk-blocked activations.
 bool ffn_blocked(const moe_dims* d) {
-  const moe::Segments routed{nullptr, d->E_local, 0, d->T, d->T * d->k};
+  const moe::Segments routed{nullptr, d->E_local, 0, d->T, d->T * d->k, static_cast<int>(static_cast<int64_t>(d->T) * d->k / d->E)};
   return d->T > 0 && moe::ffn_streams_weights(routed) && d->H % 16 == 0 && d->I % 16 == 0;
 }
 
@@ -183,8 +183,9 @@ FfnPlan plan_ffn(const moe_dims* d, const uint16_t* x_perm, const int32_t* x_row
   const FfnWs fw = carve_ffn(d, ws);
   const int shw = static_cast<int>(sh_width(d));
   FfnPlan p{};
-  p.routed = moe::Segments{offsets, d->E_local, 0, d->T, d->T * d->k};
-  p.shared = moe::Segments{nullptr, 1, d->T, d->T, d->T};
+  p.routed = moe::Segments{offsets, d->E_local, 0, d->T, d->T * d->k,
+                            static_cast<int>(static_cast<int64_t>(d->T) * d->k / d->E)};
+  p.shared = moe::Segments{nullptr, 1, d->T, d->T, d->T, d->T};
   p.up = moe::UpArgs{x_perm, w ? w->w_gate : nullptr, w ? w->w_up : nullptr, fw.h, d->H, d->I, x_rows,
                      rows_indexed ? d->T : 0, fw.h_blocked};
   p.sh_up = moe::UpArgs{x, w ? w->sh_gate : nullptr, w ? w->sh_up : nullptr, fw.h_sh, d->H, shw, nullptr, 0, false};
