@@ -1,5 +1,5 @@
-// Expert FFN for mid-sized batches: more rows per expert than one decode
-// step has, far fewer than fill 256-row tiles (chunked prefill, decode of
+// Expert FFN for decode and mid-sized batches: from a single token to far
+// fewer rows per expert than fill 256-row tiles (chunked prefill, decode of
 // hundreds of tokens over many experts).  What bounds it is reading the
 // active experts' weights once; hot and shared experts add MFMA work.
 //
@@ -20,9 +20,9 @@
 // stage.  Narrow items: 64-wide stages, four (<= 32 rows) or three in the
 // ring, 96 and 64 KB of weights in flight per CU.  Wide items: 32-wide stages,
 // so that three of 24 KB fit.  Splitting K over the waves as the decode kernel
-// does was slower at every size here (Qwen3 down at 256 tokens 77 us against
-// 90 and 141 with 2 and 4 parts: each part needs token rows of its own), and
-// so were 64-row chunks for hot experts (DSV2-Lite layer, 4096 tokens: 971
+// does was slower past 64 tokens (Qwen3 down at 256 tokens 77 us against 90
+// and 141 with 2 and 4 parts: each part needs token rows of its own); a batch
+// with few items halves it (see mid_splits_k).  Also slower: 64-row chunks for hot experts (DSV2-Lite layer, 4096 tokens: 971
 // against 825 us).
 //
 // Order.  Items are numbered per kind; each XCD (workgroup id mod 8) owns a
@@ -35,6 +35,10 @@
 // engines of an XCD and left the others idle half the time.  Turns of kTurn
 // items give every engine both (Qwen3 layer at 800 tokens 316 -> 286 us,
 // DSV2-Lite at 1021 tokens 448 -> 342 us).
+//
+// Only groups with rows have items: the decode kernel's grid over all groups
+// spent most of a small batch's time on empty ones (Qwen3, 1 token, layer 42.8
+// -> 34.8 us; DSV2-Lite, 1 token, gate/up 31 -> 18 us, down 35 -> 17 us).
 //
 // Measured (layer, 256-row tiles -> this kernel): Qwen3, 256 tokens 288 -> 244
 // us (gate/up streams 5.6 TB/s); DSV2-Lite, 400 tokens 341 -> 266 us; the
@@ -84,9 +88,10 @@ __device__ __forceinline__ int col_blocks(int n, int N, int cols, int wide_cols)
   return ceil_div(N, n > kWideRows ? wide_cols : cols);
 }
 
-template <bool GATED>
+template <bool GATED, int KP>
 __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mid_kernel(MidArgs ma) {
-  constexpr int OUT_COLS = GATED ? kMidCols / 2 : kMidCols;
+  constexpr int FULL_COLS = GATED ? kMidCols / 2 : kMidCols;  // output columns of 128 weight rows
+  constexpr int OUT_COLS = FULL_COLS / KP;                    // ... of a narrow item
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -99,7 +104,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   int n_wide = 0, n_narrow = 0;  // items of the routed groups
   for (int gg = lane; gg < ma.g.groups; gg += kWave) {
     const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
-    const int it = ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, 2 * OUT_COLS);
+    const int it = ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, 2 * FULL_COLS);
     n_wide += n > kWideRows ? it : 0;
     n_narrow += n > kWideRows ? 0 : it;
   }
@@ -110,15 +115,15 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   }
   n_wide = __builtin_amdgcn_readfirstlane(n_wide);
   n_narrow = __builtin_amdgcn_readfirstlane(n_narrow);
-  int n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, 2 * OUT_COLS) : 0;
-  int wide_cols = 2 * OUT_COLS;
+  int n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, 2 * FULL_COLS) : 0;
+  int wide_cols = 2 * FULL_COLS;
   if (n_shared + n_wide < kFewWide) {
-    wide_cols = OUT_COLS;
-    n_shared = sp_m > 0 ? sp_chunks * ceil_div(ma.sp.N, OUT_COLS) : 0;
+    wide_cols = FULL_COLS;
+    n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, wide_cols) : 0;
     n_wide = 0;
     for (int gg = lane; gg < ma.g.groups; gg += kWave) {
       const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
-      n_wide += n > kWideRows ? ceil_div(n, kMidRows) * ceil_div(ma.g.N, OUT_COLS) : 0;
+      n_wide += n > kWideRows ? ceil_div(n, kMidRows) * ceil_div(ma.g.N, wide_cols) : 0;
     }
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) n_wide += __shfl_xor(n_wide, off);
@@ -207,58 +212,61 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const bool segmented = kseg < K;
   const int lrow = lane & 31, lhalf = lane >> 5;
 
-  auto body = [&](auto nsub_c, auto wb_c, auto bk_c, auto depth_c) {
+  auto body = [&](auto nsub_c, auto wb_c, auto kp_c, auto bk_c, auto depth_c) {
     constexpr int NSUB = decltype(nsub_c)::value;
     constexpr int WB = decltype(wb_c)::value;
+    constexpr int NK = decltype(kp_c)::value;   // K parts; waves WN apart take the same columns
+    constexpr int WN = 4 / NK;                  // waves along the weight rows
     constexpr int BK = decltype(bk_c)::value;
     constexpr int D = decltype(depth_c)::value;
     constexpr int ROW = BK * 2;              // bytes of an LDS row
     constexpr int CPR = ROW / 16;            // 16-byte chunks per row
     constexpr int RPI = kWave / CPR;         // rows per load instruction
     constexpr int SWZ = 16 / CPR;            // rows sharing one swizzle key
-    constexpr int XPART = NSUB * 32 * ROW;   // token rows of one K part
-    constexpr int STAGE = XPART + WB * 4 * 32 * ROW;
-    constexpr int XL = NSUB * 32 / RPI / 4; // token loads per wave and stage
+    constexpr int XPART = NSUB * 32 * ROW;   // token rows of one K part   // token rows of one K part
+    constexpr int STAGE = NK * XPART + 4 * WB * 32 * ROW;
+    constexpr int XL = NSUB * 32 / RPI / WN;// token loads per wave and stage
     constexpr int WL = WB * 32 / RPI;           // weight loads per wave and stage
     constexpr int LOADS = XL + WL;
     constexpr int KS = BK / 16;              // MFMA K-steps per stage
-    static_assert(D * STAGE <= kMidLds && XL * RPI * 4 == NSUB * 32, "the ring fits, whole loads fill the token rows");
+    static_assert(D * STAGE <= kMidLds && XL * RPI * WN == NSUB * 32, "the ring fits, whole loads fill the token rows");
     const int lr = lane / CPR;               // row of a load
+    const int wn = wave % WN, wk = wave / WN;
     // 16-byte chunk c of LDS row r sits at slot c ^ ((r / SWZ) % CPR); load i
     // of the weights fills the wave's rows RPI i .., load q of the tokens the
-    // rows RPI (4 q + wave) ..
+    // rows RPI (WN q + wn) ..
     uint32_t woff[WL], xoff[XL];
     int wpiece[WL], xpiece[XL];
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
       const int r = RPI * i + lr;
-      const int b = WB * wave + r / 32;  // 32-row block of weights
+      const int b = WB * wn + r / 32;  // 32-row block of weights
       const int col = GATED ? 16 * b + (r & 15) : 32 * b + r % 32;
       woff[i] = n0 + col < N ? static_cast<uint32_t>(col * ldw * 2) : kDead;
       wpiece[i] = (lane % CPR) ^ ((r / SWZ) % CPR);
     }
 #pragma unroll
     for (int q = 0; q < XL; ++q) {
-      const int r = RPI * (4 * q + wave) + lr;
+      const int r = RPI * (WN * q + wn) + lr;
       int src = r;
       if (x_rows) src = x_rows[row_base + m0 + min(r, rows - 1)];
       xoff[q] = r < rows ? static_cast<uint32_t>(src * K * 2) : kDead;
       xpiece[q] = (lane % CPR) ^ ((r / SWZ) % CPR);
     }
-    const int nst = ceil_div(K, BK);
+    const int nst = ceil_div(ceil_div(K, BK), NK);  // stages of a K part (the last part's may lie past K)
     int s_ld = 0, slot_ld = 0;  // next stage to load and its slot
     int kb_ld = static_cast<int>((static_cast<unsigned>(nblk) * 7u + static_cast<unsigned>(g) * 3u) % static_cast<unsigned>(nst));
     auto issue = [&]() {
       unsigned char* st = smem + slot_ld * STAGE;
-      const int k0 = kb_ld * BK;
+      const int k0 = (wk * nst + kb_ld) * BK;
       const uint32_t dead = s_ld < nst ? 0u : kDead;
 #pragma unroll
       for (int q = 0; q < XL; ++q) {
         const int k = k0 + xpiece[q] * 8;
         const uint32_t kill = dead | (k < K ? 0u : kDead) | (xoff[q] & kDead);
-        load_lds16(rs_x, st + RPI * (4 * q + wave) * ROW, (xoff[q] + static_cast<uint32_t>(k * 2)) | kill);
+        load_lds16(rs_x, st + wk * XPART + RPI * (WN * q + wn) * ROW, (xoff[q] + static_cast<uint32_t>(k * 2)) | kill);
       }
-      unsigned char* wl = st + XPART + wave * (WB * 32 * ROW);
+      unsigned char* wl = st + NK * XPART + wave * (WB * 32 * ROW);
 #pragma unroll
       for (int i = 0; i < WL; ++i) {
         const int k = k0 + wpiece[i] * 8;
@@ -287,8 +295,8 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
       __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * LOADS));  // own loads of stage j landed
       stage_barrier();  // everyone's have, and everyone has read stage j - 1
       issue();          // stage j + D - 1 into the slot of stage j - 1
-      const unsigned char* xp = smem + slot * STAGE;
-      const unsigned char* wp = smem + slot * STAGE + XPART + wave * (WB * 32 * ROW);
+      const unsigned char* xp = smem + slot * STAGE + wk * XPART;
+      const unsigned char* wp = smem + slot * STAGE + NK * XPART + wave * (WB * 32 * ROW);
       bf16x8 wf[KS][WB], xf[KS][NSUB];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -309,6 +317,32 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
       if (++slot == D) slot = 0;
     }
     __builtin_amdgcn_s_waitcnt(wait_vm(0));  // the loads past the last stage: nothing may still write the LDS
+    if constexpr (NK > 1) {
+      // sum the K parts in order through LDS
+      static_assert((NK - 1) * WN * WB * NSUB * 16 * kWave * 4 <= kMidLds, "the partial sums fit the LDS");
+      float* red = reinterpret_cast<float*>(smem);
+      __syncthreads();  // every wave is past its last stage
+      if (wk > 0) {
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              red[((((wk - 1) * WN + wn) * WB + b) * NSUB + s) * (16 * kWave) + v * kWave + lane] = acc[b][s][v];
+      }
+      __syncthreads();
+      if (wk > 0) return;
+#pragma unroll
+      for (int p = 0; p < NK - 1; ++p)
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              acc[b][s][v] += red[(((p * WN + wn) * WB + b) * NSUB + s) * (16 * kWave) + v * kWave + lane];
+    }
     // ---- epilogue: lane holds C[n = 8 v4 + 4 lhalf + i][t = lrow] ----
     uint16_t* out = (shared ? ma.sp.out : ma.g.out) + static_cast<size_t>(row_base + m0) * N;
 #pragma unroll
@@ -337,7 +371,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         const auto s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
         const auto s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
         const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
-        const int col = n0 + (GATED ? 16 * (WB * wave + b) : 32 * (WB * wave + b) + 16 * p) + 8 * lhalf;
+        const int col = n0 + (GATED ? 16 * (WB * wn + b) : 32 * (WB * wn + b) + 16 * p) + 8 * lhalf;
         if (r < rows && col < N) store16(out + static_cast<size_t>(r) * N + col, v);
       }
     }
@@ -350,21 +384,24 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   using C5 = integral_constant<int, 5>;
   using K32 = integral_constant<int, 32>;
   using K64 = integral_constant<int, 64>;
-  if (wide && wide_cols > OUT_COLS)
-    body(C4{}, C2{}, K32{}, C3{});
+  if (wide && wide_cols > FULL_COLS)
+    body(C4{}, C2{}, C1{}, K32{}, C3{});
   else if (wide)
-    body(C4{}, C1{}, K32{}, C5{});
-  else if (rows > 32)
-    body(C2{}, C1{}, K64{}, C3{});
-  else
-    body(C1{}, C1{}, K64{}, C4{});
+    body(C4{}, C1{}, C1{}, K32{}, C5{});
+  else if constexpr (KP == 1) {
+    if (rows > 32) body(C2{}, C1{}, C1{}, K64{}, C3{});
+    else body(C1{}, C1{}, C1{}, K64{}, C4{});
+  } else {
+    if (rows > 32) body(C2{}, C1{}, C2{}, K32{}, C5{});
+    else body(C1{}, C1{}, C2{}, K64{}, C3{});
+  }
 }
 
-template <bool GATED>
+template <bool GATED, int KP>
 hipError_t launch_mid_t(const Segments& seg, const GemmArgs& g, const GemmArgs& sp, hipStream_t st) {
-  constexpr int OUT_COLS = GATED ? kMidCols / 2 : kMidCols;
+  constexpr int OUT_COLS = (GATED ? kMidCols / 2 : kMidCols) / KP;
   static unsigned long long lds_set = 0;  // devices with the LDS limit raised
-  const hipError_t e = set_max_dynamic_lds(reinterpret_cast<const void*>(&mid_kernel<GATED>), kMidLds, &lds_set);
+  const hipError_t e = set_max_dynamic_lds(reinterpret_cast<const void*>(&mid_kernel<GATED, KP>), kMidLds, &lds_set);
   if (e != hipSuccess) return e;
   // at most one partly filled chunk per group; wide items need fewer column blocks
   const long long chunks = seg.total_rows / kMidRows + std::min(seg.groups, seg.total_rows);
@@ -372,16 +409,48 @@ hipError_t launch_mid_t(const Segments& seg, const GemmArgs& g, const GemmArgs& 
   if (sp.static_rows > 0) items += static_cast<long long>(ceil_div(sp.static_rows, kMidRows)) * ceil_div(sp.N, OUT_COLS);
   const long long per_xcd = items / kXcds + 3;  // each kind's run rounds up by one
   if (items == 0) return hipSuccess;
-  hipLaunchKernelGGL((mid_kernel<GATED>), dim3(static_cast<unsigned>(per_xcd * kXcds)), dim3(kMidThreads), kMidLds,
+  hipLaunchKernelGGL((mid_kernel<GATED, KP>), dim3(static_cast<unsigned>(per_xcd * kXcds)), dim3(kMidThreads), kMidLds,
                      st, MidArgs{g, sp});
   return hipGetLastError();
 }
 
+// Narrow items that an evenly routed batch makes (undivided in K).
+long long narrow_items(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+  const int cols = gated ? kMidCols / 2 : kMidCols;
+  return static_cast<long long>(seg.hit_groups) * ceil_div(a.N, cols) + (sh ? ceil_div(sh->N, cols) : 0);
+}
+
+// Few narrow items leave CUs idle and each runs through its whole K alone:
+// half as many columns and the K halves on two pairs of waves then.  Time
+// without / with the split: Qwen3, 1 token (96 and 128 items) gate/up 18.0 /
+// 14.7 us, down 10.1 / 8.8, 2 tokens (180) gate/up 19.5 / 21.1; long K:
+// Mixtral down, 1, 4 and 8 tokens (70, 175, 230) 83.6 / 59.0, 96 / 80 and 112
+// / 124 us; DSV3 share gate/up, 14 and 24 tokens (400, 610) 120 / 110 and 130
+// / 131 us; a stacked K of the shared experts (DSV2-Lite down, K 2816 among
+// 1408), 12 tokens (730) 38 / 31 us.
+bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+  if (seg.max_rows > kWideRows) return false;
+  const long long items = narrow_items(seg, a, sh, gated);
+  return items <= 128 || (a.K >= kLongK && items <= (gated ? 400 : 200)) || (sh && sh->K > a.K && items <= 768);
+}
+
 }  // namespace
+
+// Batches of up to 64 tokens: everything but the gate/up projection of few,
+// wide experts, where the decode kernel's finer items still stream best
+// (Mixtral, time of this kernel over that one's: 1.02 at 8 to 24 tokens, 1.00
+// to 1.02 at 40 to 64, where the rest of the range is 0.6 to 1.0: Qwen3 gate/up
+// 0.99 at 64, DSV2-Lite 0.60 at 1 and 0.85 at 40, DSV3 share 0.81 at 64).
+bool mid_streams(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+  return !(gated && !sh && a.K >= kLongK && narrow_items(seg, a, sh, gated) >= 1024);
+}
 
 hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st) {
   const GemmArgs none{};
-  return gated ? launch_mid_t<true>(seg, a, sh ? *sh : none, st) : launch_mid_t<false>(seg, a, sh ? *sh : none, st);
+  const GemmArgs& sp = sh ? *sh : none;
+  if (mid_splits_k(seg, a, sh, gated))
+    return gated ? launch_mid_t<true, 2>(seg, a, sp, st) : launch_mid_t<false, 2>(seg, a, sp, st);
+  return gated ? launch_mid_t<true, 1>(seg, a, sp, st) : launch_mid_t<false, 1>(seg, a, sp, st);
 }
 
 }  // namespace moe

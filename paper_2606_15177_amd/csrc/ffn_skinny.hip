@@ -1,4 +1,6 @@
-// Expert FFN for decode-sized batches: weight streaming.
+// Expert FFN for decode-sized batches of few, wide experts (the gate/up
+// projection of a Mixtral-shaped layer, see mid_streams): weight streaming.
+// Also takes the decode sizes whose row offsets pass 32 bits.
 //
 // With at most a few dozen rows per expert the grouped GEMM is bound by
 // reading the active experts' weights from HBM exactly once.  The weights take
@@ -56,19 +58,6 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
   }
   if (m <= 0) return;  // an expert with no rows costs no weight traffic
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-  // first chunk of this group in the chunk-blocked layouts: the chunks of the
-  // groups before it (every wave, lanes over groups)
-  int chunk_base = 0;
-  if (a.x_blocked || a.out_blocked) {
-    for (int g0 = 0; g0 < g; g0 += kWave) {
-      const int gg = g0 + lane;
-      int c = gg < g ? ceil_div(a.offsets[gg + 1] - a.offsets[gg], kChunkRows) : 0;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-      chunk_base += c;
-    }
-  }
-
   const int part = wave;
   const int n0 = blockIdx.x * WG_ROWS;
   const int nks = ceil_div(a.K, KS);
@@ -131,23 +120,16 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
   for (int tok0 = 0; tok0 < m; tok0 += 64) {
     const int mc = min(64, m - tok0);
     const int nch = mc > 32 ? 2 : 1;
-    // per chunk: the lane's 16 bytes of the step's first MFMA B operand; the
-    // following K-steps sit kstride elements further
+    // per chunk of 32 rows: the lane's 16 bytes of the step's first MFMA B operand
     const uint16_t* xrow[2];
     bool tok_ok[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int tok = tok0 + c * 32 + (lane & 31);
-      if (a.x_blocked) {  // chunk rows past m are zeros
-        tok_ok[c] = c < nch;
-        xrow[c] = a.x + static_cast<size_t>(chunk_base + tok0 / kChunkRows + c) * (a.K / 16) * kBlockElems + lane * 8;
-      } else {
-        tok_ok[c] = c < nch && tok < m;
-        const int r = row_base + (tok_ok[c] ? tok : 0);
-        xrow[c] = a.x + static_cast<size_t>(a.x_rows ? a.x_rows[r] : r) * a.K + 8 * (lane >> 5);
-      }
+      tok_ok[c] = c < nch && tok < m;
+      const int r = row_base + (tok_ok[c] ? tok : 0);
+      xrow[c] = a.x + static_cast<size_t>(a.x_rows ? a.x_rows[r] : r) * a.K + 8 * (lane >> 5);
     }
-    const int kstride = a.x_blocked ? kBlockElems : 16;  // elements between consecutive 16-wide K-steps
 
     f32x16 acc[NB][2];
 #pragma unroll
@@ -170,7 +152,7 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
           if (c == 1 && nch < 2) break;
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk)
-            dst[c][kk] = load16(xrow[c] + (x_ok(kb, c, kk) ? (kb * (KS / 16) + kk) * kstride : 0));
+            dst[c][kk] = load16(xrow[c] + (x_ok(kb, c, kk) ? (kb * (KS / 16) + kk) * 16 : 0));
         }
       };
       auto step = [&](int j, u32x4 (&cur)[2][KK], u32x4 (&nxt)[2][KK]) {
@@ -232,7 +214,7 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
           for (int kk = 0; kk < KK; ++kk) {
             const int k = kb * KS + 16 * kk + 8 * (lane >> 5);
             const u32x4 zero = {0u, 0u, 0u, 0u};
-            xt[c][kk] = (tok_ok[c] && k < a.K) ? load16(xrow[c] + (kb * (KS / 16) + kk) * kstride) : zero;
+            xt[c][kk] = (tok_ok[c] && k < a.K) ? load16(xrow[c] + (kb * (KS / 16) + kk) * 16) : zero;
           }
         // keep DEPTH-1 steps in flight; the slot refilled is the one step j-1
         // read, whose fragments are in registers by now
@@ -275,10 +257,8 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int tok = tok0 + c * 32 + (lane & 31);
-        if (c >= nch || (!a.out_blocked && tok >= m)) continue;
+        if (c >= nch || tok >= m) continue;
         uint16_t* orow = a.out + static_cast<size_t>(row_base + tok) * a.N;
-        uint16_t* oblk = a.out + static_cast<size_t>(chunk_base + tok0 / kChunkRows + c) * (a.N / 16) * kBlockElems +
-                         8 * (lane & 31);
         constexpr int NOUT = GATED ? 1 : NB;  // 32-column output blocks
 #pragma unroll
         for (int ob = 0; ob < NOUT; ++ob)
@@ -299,9 +279,7 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
             uint2 pk;
             pk.x = pack_bf16x2(o[0], o[1]);
             pk.y = pack_bf16x2(o[2], o[3]);
-            // blocked: columns n..n+3 of row t go to block n/16, lane 32*((n/8)&1) + t, values n%8..
-            uint16_t* dst = a.out_blocked ? oblk + (n >> 4) * kBlockElems + 256 * ((n >> 3) & 1) + (n & 7) : orow + n;
-            *reinterpret_cast<uint2*>(dst) = pk;
+            *reinterpret_cast<uint2*>(orow + n) = pk;
           }
       }
     }
@@ -328,12 +306,7 @@ hipError_t launch_skinny_t(const Segments& seg, const GemmArgs& a, hipStream_t s
 
 }  // namespace
 
-size_t chunk_capacity(int groups, int total_rows) {
-  return static_cast<size_t>(total_rows / kChunkRows) + static_cast<size_t>(std::min(groups, total_rows));
-}
-
 bool skinny_ok(const GemmArgs& a) {
-  if ((a.x_blocked || a.out_blocked) && (a.K % 16 != 0 || (a.out_blocked && a.N % 16 != 0))) return false;
   // weight byte offsets within a group are 32-bit
   const size_t w_span = (static_cast<size_t>(a.N) * a.ldw +
                          (a.kseg < a.K ? static_cast<size_t>((a.K - 1) / a.kseg) * a.seg_stride : 0) + a.K) * 2;
@@ -341,11 +314,6 @@ bool skinny_ok(const GemmArgs& a) {
 }
 
 hipError_t launch_skinny(const Segments& seg, const GemmArgs& a, bool gated, hipStream_t st) {
-  // the blocked layouts are defined by the device-side offsets
-  if ((a.x_blocked || a.out_blocked) && a.offsets == nullptr) return hipErrorInvalidValue;
-  // the gate/up kernel's out-of-range token lanes read their row's first
-  // piece, which exists only in the row layout
-  if (gated && a.x_blocked) return hipErrorInvalidValue;
   if (!skinny_ok(a)) return hipErrorInvalidValue;
   // gate/up: the gate and up blocks of 32 rows per wave; down: two 32-row
   // blocks per wave; 4 K parts, 64-wide steps, two-step rings (64 KB of LDS,

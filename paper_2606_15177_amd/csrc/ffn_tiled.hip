@@ -85,7 +85,7 @@ constexpr int kMaxGroups = 1024;
 //     DSV2-Lite 1.64 at 85, 1.16 at 303, 0.97 at 363; DSV3 share 1.21 at 91,
 //     1.04 at 212, 0.96 at 303.
 constexpr int kMidMean = 40, kMidMeanUp = 160, kMidMeanShared = 256;
-constexpr int kHalfTailK = 4096;  // K from which grouped launches take half tail tiles
+constexpr int kHalfTailK = kLongK;  // K from which grouped launches take half tail tiles
 constexpr int kBlockM = 8;           // m-tiles per block of a static group's tile order
 
 // One K stage and the ring of its parts.
@@ -1090,12 +1090,11 @@ hipError_t launch_pfx(const TiledArgs& ta, long long grid, hipStream_t st) {
   }
 }
 
-// Host-side checks of one problem: no blocked layouts, at most kMaxGroups
-// groups, and 32-bit byte offsets for a tile's X rows (all x_row_count rows
+// Host-side checks of one problem: at most kMaxGroups groups, and 32-bit byte offsets for a tile's X rows (all x_row_count rows
 // of x when rows are indexed), a group's weight columns and a tile's output
 // rows.
 bool tiled_ok(const Segments& seg, const GemmArgs& a) {
-  if (seg.groups > kMaxGroups || a.x_blocked || a.out_blocked) return false;
+  if (seg.groups > kMaxGroups) return false;
   // grouped problems: tail tiles read 2 kBN weight rows, and only a single K segment
   if (a.static_rows == 0 && a.kseg < a.K) return false;
   const size_t x_span = static_cast<size_t>(a.x_row_count > 0 ? a.x_row_count : kBM) * a.K * 2;
@@ -1128,7 +1127,6 @@ GemmArgs up_gemm(const Segments& seg, const UpArgs& u) {
   a.x = u.x;
   a.x_rows = u.x_rows;
   a.x_row_count = u.x_row_count;
-  a.out_blocked = u.h_blocked;
   a.offsets = seg.offsets;
   a.static_rows = seg.static_rows;
   a.groups = seg.groups;
@@ -1147,7 +1145,6 @@ GemmArgs up_gemm(const Segments& seg, const UpArgs& u) {
 GemmArgs down_gemm(const Segments& seg, const DownArgs& d) {
   GemmArgs a{};
   a.x = d.h;
-  a.x_blocked = d.h_blocked;
   a.offsets = seg.offsets;
   a.static_rows = seg.static_rows;
   a.groups = seg.groups;
@@ -1164,11 +1161,8 @@ GemmArgs down_gemm(const Segments& seg, const DownArgs& d) {
 }
 
 bool up_ok(const Segments& seg, const UpArgs& u) {
-  if (u.h_blocked && !ffn_streams_weights(seg)) return false;
   return !(u.x_rows && (seg.offsets == nullptr || u.x_row_count <= 0));
 }
-
-bool down_ok(const Segments& seg, const DownArgs& d) { return !(d.h_blocked && !ffn_streams_weights(seg)); }
 
 // The limits of the kernel a problem runs on (weight streaming or tiled).
 // Whether one launch takes two problems or each its own, each problem must
@@ -1177,10 +1171,13 @@ bool gemm_ok(const Segments& seg, const GemmArgs& a) {
   return ffn_streams_weights(seg) ? skinny_ok(a) : tiled_ok(seg, a);
 }
 
-// Whether a grouped problem past the weight-streaming sizes takes the
-// mid-sized kernel (ffn_mid.hip) rather than 256-row tiles; `sh` joins it.
-bool takes_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+// Whether a grouped problem takes the mid-sized kernel (ffn_mid.hip) rather
+// than 256-row tiles or, in decode batches, the decode kernel; `sh` joins it.
+bool takes_mid(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh, bool gated) {
   if (a.static_rows > 0 || (sh && sh->static_rows == 0)) return false;
+  // 32-bit offsets (the decode kernel accepts larger ones)
+  if (!tiled_ok(seg, a) || (sh && !tiled_ok(*sh_seg, *sh))) return false;
+  if (ffn_streams_weights(seg)) return mid_streams(seg, a, sh, gated);
   if (seg.mean_rows <= kMidMean) return true;
   if (!gated && sh) {
     const long long wr = static_cast<long long>(seg.groups) * a.K;
@@ -1204,10 +1201,7 @@ bool takes_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool 
 hipError_t launch_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh,
                         bool gated, hipStream_t st) {
   const bool tiled = !ffn_streams_weights(seg);
-  if (tiled && takes_mid(seg, a, sh, gated)) {
-    if (!tiled_ok(seg, a) || (sh && !tiled_ok(*sh_seg, *sh))) return hipErrorInvalidValue;
-    return launch_mid(seg, a, sh, gated, st);
-  }
+  if (takes_mid(seg, a, sh_seg, sh, gated)) return launch_mid(seg, a, sh, gated, st);
   const int out_cols = gated ? kBN / 2 : kBN;
   const bool merge = sh != nullptr && tiled && !ffn_streams_weights(*sh_seg) && sh_seg->offsets == nullptr &&
                      static_cast<long long>(ceil_div(sh_seg->static_rows, kBM)) * ceil_div(sh->N, out_cols) %
@@ -1235,7 +1229,7 @@ bool ffn_streams_weights(const Segments& seg) { return seg.max_rows <= kSkinnyMa
 bool ffn_up_supported(const Segments& seg, const UpArgs& u) { return up_ok(seg, u) && gemm_ok(seg, up_gemm(seg, u)); }
 
 bool ffn_down_supported(const Segments& seg, const DownArgs& d) {
-  return down_ok(seg, d) && gemm_ok(seg, down_gemm(seg, d));
+  return gemm_ok(seg, down_gemm(seg, d));
 }
 
 hipError_t launch_ffn_up(const Segments& seg, const UpArgs& u, hipStream_t st) {
@@ -1251,13 +1245,11 @@ hipError_t launch_ffn_up2(const Segments& seg, const UpArgs& u, const Segments& 
 }
 
 hipError_t launch_ffn_down(const Segments& seg, const DownArgs& d, hipStream_t st) {
-  if (!down_ok(seg, d)) return hipErrorInvalidValue;
   return launch_gemm2(seg, down_gemm(seg, d), nullptr, nullptr, false, st);
 }
 
 hipError_t launch_ffn_down2(const Segments& seg, const DownArgs& d, const Segments& sh_seg, const DownArgs& sh,
                             hipStream_t st) {
-  if (!down_ok(seg, d) || !down_ok(sh_seg, sh)) return hipErrorInvalidValue;
   const GemmArgs s = down_gemm(sh_seg, sh);
   return launch_gemm2(seg, down_gemm(seg, d), &sh_seg, &s, false, st);
 }

@@ -72,8 +72,9 @@ hipError_t launch_gather_rows(int capacity, int H, const int32_t* perm_token,
 // offsets[g+1]) of the activation matrix (or rows [0, static_rows) of a single
 // group when offsets == nullptr).  max_rows bounds the rows of any one group
 // and total_rows the rows of all groups (both host-side capacities);
-// mean_rows is what a group holds on average when routing is even (a choice
-// of kernel only: any distribution is correct).
+// mean_rows and hit_groups are what a group holds on average and how many
+// groups get rows when routing is even (for the choice of a kernel only: any
+// distribution is correct).
 struct Segments {
   const int32_t* offsets;
   int groups;
@@ -81,6 +82,7 @@ struct Segments {
   int max_rows;
   int total_rows;
   int mean_rows;
+  int hit_groups;
 };
 
 // h[r][i] = silu(sum_c X[r][c] Wg[g][i][c]) * (sum_c X[r][c] Wu[g][i][c]),
@@ -95,8 +97,6 @@ struct UpArgs {
   int K, N;
   const int32_t* x_rows;
   int x_row_count;
-  // write h in the chunk-blocked layout (decode-sized groups, see below)
-  bool h_blocked;
 };
 hipError_t launch_ffn_up(const Segments& seg, const UpArgs& a, hipStream_t st);
 // Host only, no HIP call: whether launch_ffn_up accepts these sizes (the
@@ -108,18 +108,8 @@ bool ffn_up_supported(const Segments& seg, const UpArgs& a);
 // shared tiles first.
 hipError_t launch_ffn_up2(const Segments& seg, const UpArgs& a, const Segments& sh_seg, const UpArgs& sh,
                           hipStream_t st);
-// True when these segments take the weight-streaming kernels (decode-sized
-// groups).
+// True for decode-sized groups (at most 64 rows each).
 bool ffn_streams_weights(const Segments& seg);
-
-// For decode-sized groups (ffn_streams_weights) the gate/up GEMM may write h
-// chunk-blocked: each group's rows cut into chunks of 32 (the last one
-// zero-padded) whose 1 KB blocks are MFMA operand fragments, which the down
-// GEMM then loads as whole contiguous kilobytes.  Such an h holds
-// chunk_capacity(groups, total_rows) chunks of 32 x N; N and the down GEMM's
-// K must be multiples of 16.
-size_t chunk_capacity(int groups, int total_rows);
-constexpr int kChunkRowsHost = 32;  // rows of a chunk of the blocked layout
 
 // y[r][n] = sum_c h[r][c] Wd(g, n, c), h row stride K, y row stride N.
 // Wd(g, n, c) = w[g*group_stride + (c / kseg)*seg_stride + n*ldw + c % kseg]
@@ -131,8 +121,6 @@ struct DownArgs {
   uint16_t* y;
   int K, N, kseg, ldw;
   size_t seg_stride, group_stride;
-  // h in the chunk-blocked layout written by launch_ffn_up
-  bool h_blocked;
 };
 hipError_t launch_ffn_down(const Segments& seg, const DownArgs& a, hipStream_t st);
 // Host only: whether launch_ffn_down accepts these sizes (as above).

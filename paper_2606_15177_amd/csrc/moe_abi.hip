@@ -4,6 +4,7 @@
 #include "moe.h"
 
 #include <algorithm>
+#include <cmath>
 
 #include "kernels.h"
 
@@ -55,17 +56,19 @@ int64_t sh_width(const moe_dims* d) {
   return d->n_shared > 0 ? static_cast<int64_t>(d->n_shared) * d->I_shared : 0;
 }
 
-// Decode-sized batches run the routed GEMMs on chunk-blocked activations.
-bool ffn_blocked(const moe_dims* d) {
-  const moe::Segments routed{nullptr, d->E_local, 0, d->T, d->T * d->k, static_cast<int>(static_cast<int64_t>(d->T) * d->k / d->E)};
-  return d->T > 0 && moe::ffn_streams_weights(routed) && d->H % 16 == 0 && d->I % 16 == 0;
+// Rows that the workspace holds for h.  Decode-sized batches reserve every
+// expert's rows in whole chunks of 32: more than they fill now, but the size
+// decides what moe_forward_noalloc accepts, which stays as it was.
+size_t h_rows(const moe_dims* d) {
+  const size_t rows = static_cast<size_t>(d->T) * d->k;
+  const moe::Segments routed{nullptr, d->E_local, 0, d->T, d->T * d->k, 0, 0};
+  if (d->T == 0 || !moe::ffn_streams_weights(routed) || d->H % 16 != 0 || d->I % 16 != 0) return rows;
+  return (rows / 32 + std::min<size_t>(d->E_local, rows)) * 32;
 }
 
-// Workspace of the expert FFN: h (chunk-blocked for decode-sized batches),
-// then h_shared.
+// Workspace of the expert FFN: h, then h_shared.
 struct FfnWs {
   uint16_t* h;
-  bool h_blocked;
   uint16_t* h_sh;
   size_t bytes;
 };
@@ -78,14 +81,7 @@ FfnWs carve_ffn(const moe_dims* d, void* base) {
     off += align_up(bytes);
     return r;
   };
-  const size_t rows = static_cast<size_t>(d->T) * d->k;
-  w.h_blocked = ffn_blocked(d);
-  if (w.h_blocked) {
-    const size_t chunk_rows = moe::chunk_capacity(d->E_local, static_cast<int>(rows)) * moe::kChunkRowsHost;
-    w.h = reinterpret_cast<uint16_t*>(take(chunk_rows * d->I * sizeof(uint16_t)));
-  } else {
-    w.h = reinterpret_cast<uint16_t*>(take(rows * d->I * sizeof(uint16_t)));
-  }
+  w.h = reinterpret_cast<uint16_t*>(take(h_rows(d) * d->I * sizeof(uint16_t)));
   w.h_sh = reinterpret_cast<uint16_t*>(take(static_cast<size_t>(d->T) * sh_width(d) * sizeof(uint16_t)));
   w.bytes = off;
   return w;
@@ -183,16 +179,18 @@ FfnPlan plan_ffn(const moe_dims* d, const uint16_t* x_perm, const int32_t* x_row
   const FfnWs fw = carve_ffn(d, ws);
   const int shw = static_cast<int>(sh_width(d));
   FfnPlan p{};
-  p.routed = moe::Segments{offsets, d->E_local, 0, d->T, d->T * d->k,
-                            static_cast<int>(static_cast<int64_t>(d->T) * d->k / d->E)};
-  p.shared = moe::Segments{nullptr, 1, d->T, d->T, d->T, d->T};
+  // rows per expert and experts hit, if routing were even
+  const int mean = static_cast<int>(static_cast<int64_t>(d->T) * d->k / d->E);
+  const int hit = static_cast<int>(std::ceil(d->E_local * (1.0 - std::pow(1.0 - static_cast<double>(d->k) / d->E, d->T))));
+  p.routed = moe::Segments{offsets, d->E_local, 0, d->T, d->T * d->k, mean, hit};
+  p.shared = moe::Segments{nullptr, 1, d->T, d->T, d->T, d->T, 1};
   p.up = moe::UpArgs{x_perm, w ? w->w_gate : nullptr, w ? w->w_up : nullptr, fw.h, d->H, d->I, x_rows,
-                     rows_indexed ? d->T : 0, fw.h_blocked};
-  p.sh_up = moe::UpArgs{x, w ? w->sh_gate : nullptr, w ? w->sh_up : nullptr, fw.h_sh, d->H, shw, nullptr, 0, false};
+                     rows_indexed ? d->T : 0};
+  p.sh_up = moe::UpArgs{x, w ? w->sh_gate : nullptr, w ? w->sh_up : nullptr, fw.h_sh, d->H, shw, nullptr, 0};
   p.dn = moe::DownArgs{fw.h, w ? w->w_down : nullptr, y_perm, d->I, d->H, d->I, d->I, 0,
-                       static_cast<size_t>(d->H) * d->I, fw.h_blocked};
+                       static_cast<size_t>(d->H) * d->I};
   p.sh_dn = moe::DownArgs{fw.h_sh, w ? w->sh_down : nullptr, y_shared, shw, d->H, d->I_shared, d->I_shared,
-                          static_cast<size_t>(d->H) * d->I_shared, 0, false};
+                          static_cast<size_t>(d->H) * d->I_shared, 0};
   return p;
 }
 

@@ -47,3 +47,14 @@ def test_mid_group_mixes(moe, sizes):  # noqa: F811
 ])
 def test_tile_boundaries_on_the_tiled_kernel(moe, H, I):  # noqa: F811
     _sized(moe, TILE_EDGES, H, I)
+
+
+@pytest.mark.parametrize("sizes", [[64], [33, 31], [1, 31, 32], [0, 50, 2], [3] * 20, [1]])
+@pytest.mark.parametrize("H,I,n_sh,I_sh", [
+    (136, 200, 0, 0),       # few items: K in two halves
+    (8, 8, 1, 8),           # ... one half empty
+    (264, 520, 0, 0),       # with 20 groups: K whole for gate/up
+    (4104, 72, 2, 40),      # long K with a ragged second half; shared rows, a stacked K
+])
+def test_decode_batches(moe, sizes, H, I, n_sh, I_sh):  # noqa: F811
+    _sized(moe, sizes, H, I, n_sh, I_sh)
