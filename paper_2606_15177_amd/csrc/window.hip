@@ -16,7 +16,7 @@
 namespace moe {
 namespace {
 
-constexpr int kWinThreads = 256;
+constexpr int kWinThreads = 1024;
 constexpr int kWinWaves = kWinThreads / kWave;
 
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
@@ -44,6 +44,7 @@ __global__ __launch_bounds__(kWinThreads) void window_layer_kernel(WindowArgs a)
       b = a.B[static_cast<size_t>(l) * E + e];
     } else {
       b = 0;
+#pragma unroll 8
       for (int s = 0; s < S; ++s) b += A_l[static_cast<size_t>(s) * E + e];
     }
     const int g = xs[e];
@@ -55,10 +56,19 @@ __global__ __launch_bounds__(kWinThreads) void window_layer_kernel(WindowArgs a)
     const bool home_ok = home >= 0 && home < G;
     const int64_t* row = A_l + static_cast<size_t>(s) * E;
     int64_t tot = 0, rem = 0;
-    for (int e = lane; e < E; e += kWave) {
-      const int64_t c = row[e];
-      tot += c;
-      rem += (!home_ok || xs[e] != home) ? c : 0;
+    // four loads in flight per lane; past the row's end an element in range,
+    // dropped
+    for (int e0 = lane; e0 < E; e0 += 4 * kWave) {
+      int64_t c[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = row[min(e0 + j * kWave, E - 1)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int e = e0 + j * kWave;
+        if (e >= E) continue;
+        tot += c[j];
+        rem += (!home_ok || xs[e] != home) ? c[j] : 0;
+      }
     }
     tot = wave_sum_i64(tot);
     rem = wave_sum_i64(rem);
@@ -86,10 +96,11 @@ __global__ __launch_bounds__(kWinThreads) void window_pressure_kernel(WindowArgs
     if (d >= 0 && d < D) atomicAdd(&eng[d], static_cast<unsigned long long>(a.rank_load[i]));
   }
   __syncthreads();
-  if (tid == 0) {
+  if (tid < kWave) {
     int64_t all = 0;
-    for (int d = 0; d < D; ++d) all += static_cast<int64_t>(eng[d]);
-    all_s = all;
+    for (int d = tid; d < D; d += kWave) all += static_cast<int64_t>(eng[d]);
+    all = wave_sum_i64(all);
+    if (tid == 0) all_s = all;
   }
   __syncthreads();
   const int64_t all = all_s;
