@@ -178,11 +178,29 @@ constexpr int kScatterWaves = kTile / kWave;
 // kInlineLoads loads (tiles x slots / (4 kTile)), all in flight at once
 constexpr int kInlineLoads = 8;
 constexpr long long kInlineScanMax = 4LL * kTile * kInlineLoads;
+// Slots per load of the inline scan: the rows of counts are 16-byte aligned
+// only where the slots divide by four.
+__host__ __device__ constexpr int inline_scan_slots(int E_local) { return E_local % 4 == 0 ? 4 : 1; }
+// W threads take a row of counts.  One slot per load (any E_local) takes a
+// quarter of the counts within one batch of loads; the scan launch that it
+// saves cost more (2331 pairs on 10 slots: scan and scatter 2.6 + 5.1 us,
+// inline 5.2 us).
+__host__ __device__ constexpr int inline_scan_width(int E_local) { return E_local / inline_scan_slots(E_local); }
+// Rows of threads: as few as take all tiles in one batch of loads, since a
+// slot's partial sums are added up row by row (4000 pairs on 8 slots: scatter
+// 10.6 us with all of kTile / W = 256 rows, 6.1 so).
+__device__ __forceinline__ int inline_scan_rows(int n_tiles, int E_local) {
+  return min(kTile / inline_scan_width(E_local), ceil_div(n_tiles, kInlineLoads));
+}
+bool scan_inline(int n_tiles, int E_local) {
+  return inline_scan_width(E_local) <= kTile &&
+         static_cast<long long>(n_tiles) * inline_scan_width(E_local) <= kInlineScanMax / 4;
+}
 
 // inline_scan: tile_prefix holds the count pass's raw per-tile counts (no
 // scan pass ran); each block sums, per slot, the counts of the tiles before
-// its own and of all tiles itself (E_local a multiple of 4, at most
-// 4 kTile).  Else tile_prefix and slot_total come from the scan pass.
+// its own and of all tiles itself (see scan_inline).  Else tile_prefix and
+// slot_total come from the scan pass.
 // RED: blocks past the tiles sum the statistics (see StatsReduce); without
 // it the kernel has no such branch.
 template <bool RED>
@@ -217,34 +235,55 @@ __global__ __launch_bounds__(kTile) void perm_scatter_kernel(
   const int e_p = topk_idx[p < n_pairs ? p : 0];
   for (int i = threadIdx.x; i < kScatterWaves * E_local; i += blockDim.x) mask[i] = 0;
   if (inline_scan) {
-    // thread (row r, slots 4 sl .. 4 sl + 3) sums tiles r, r + R, ... (R
-    // rows of E_local / 4 threads), 16 bytes per load, one batch of loads
-    // (see kInlineLoads); rows then add up through LDS
-    const int W = E_local / 4;
-    const int R = kTile / W;
+    // thread (row r, slots 4 sl .. 4 sl + 3, or slot sl) sums tiles r, r + R,
+    // ..., one batch of loads (see kInlineLoads); rows then add up through LDS
+    const int W = inline_scan_width(E_local);
+    const int R = inline_scan_rows(n_tiles, E_local);
     const int r = threadIdx.x / W, sl = threadIdx.x - r * W;
-    int4 before = {0, 0, 0, 0}, all = {0, 0, 0, 0};
-    if (r < R) {
-      for (int t0 = r; t0 < n_tiles; t0 += kInlineLoads * R) {
-        int4 v[kInlineLoads];
+    if (inline_scan_slots(E_local) == 1) {
+      int before = 0, all = 0;
+      if (r < R) {
+        for (int t0 = r; t0 < n_tiles; t0 += kInlineLoads * R) {
+          int v[kInlineLoads];
 #pragma unroll
-        for (int u = 0; u < kInlineLoads; ++u) {
-          const int tt = t0 + u * R;
-          v[u] = *reinterpret_cast<const int4*>(tile_prefix + static_cast<size_t>(tt < n_tiles ? tt : 0) * E_local +
-                                                4 * sl);
-        }
+          for (int u = 0; u < kInlineLoads; ++u) {
+            const int tt = t0 + u * R;
+            v[u] = tile_prefix[static_cast<size_t>(tt < n_tiles ? tt : 0) * E_local + sl];
+          }
 #pragma unroll
-        for (int u = 0; u < kInlineLoads; ++u) {
-          const int tt = t0 + u * R;
-          const int4 c = tt < n_tiles ? v[u] : int4{0, 0, 0, 0};
-          all.x += c.x; all.y += c.y; all.z += c.z; all.w += c.w;
-          if (tt < tile) {
-            before.x += c.x; before.y += c.y; before.z += c.z; before.w += c.w;
+          for (int u = 0; u < kInlineLoads; ++u) {
+            const int tt = t0 + u * R;
+            all += tt < n_tiles ? v[u] : 0;
+            before += tt < tile ? v[u] : 0;
           }
         }
+        part[r * E_local + sl] = before;
+        part[(R + r) * E_local + sl] = all;
       }
-      *reinterpret_cast<int4*>(part + r * E_local + 4 * sl) = before;
-      *reinterpret_cast<int4*>(part + (R + r) * E_local + 4 * sl) = all;
+    } else {
+      int4 before = {0, 0, 0, 0}, all = {0, 0, 0, 0};
+      if (r < R) {
+        for (int t0 = r; t0 < n_tiles; t0 += kInlineLoads * R) {
+          int4 v[kInlineLoads];
+#pragma unroll
+          for (int u = 0; u < kInlineLoads; ++u) {
+            const int tt = t0 + u * R;
+            v[u] = *reinterpret_cast<const int4*>(tile_prefix + static_cast<size_t>(tt < n_tiles ? tt : 0) * E_local +
+                                                  4 * sl);
+          }
+#pragma unroll
+          for (int u = 0; u < kInlineLoads; ++u) {
+            const int tt = t0 + u * R;
+            const int4 c = tt < n_tiles ? v[u] : int4{0, 0, 0, 0};
+            all.x += c.x; all.y += c.y; all.z += c.z; all.w += c.w;
+            if (tt < tile) {
+              before.x += c.x; before.y += c.y; before.z += c.z; before.w += c.w;
+            }
+          }
+        }
+        *reinterpret_cast<int4*>(part + r * E_local + 4 * sl) = before;
+        *reinterpret_cast<int4*>(part + (R + r) * E_local + 4 * sl) = all;
+      }
     }
   }
   build_slot_map(slot_of, E, E_local, local_experts);  // (ends with a barrier)
@@ -255,7 +294,7 @@ __global__ __launch_bounds__(kTile) void perm_scatter_kernel(
     int tot = 0, pre = 0;
     if (s < E_local) {
       if (inline_scan) {
-        const int R = kTile / (E_local / 4);
+        const int R = inline_scan_rows(n_tiles, E_local);
         for (int r = 0; r < R; ++r) {
           pre += part[r * E_local + s];
           tot += part[(R + r) * E_local + s];
@@ -382,8 +421,7 @@ hipError_t launch_permute(int T, int k, int E, int E_local, const int32_t* local
   int32_t* slot_total = tile_counts + static_cast<size_t>(n_tiles) * E_local;
   // few tiles x slots: each scatter block sums the counts it needs itself,
   // which saves the scan launch
-  const bool inline_scan = E_local % 4 == 0 && E_local <= 4 * kTile &&
-                           static_cast<long long>(n_tiles) * E_local <= kInlineScanMax;
+  const bool inline_scan = scan_inline(n_tiles, E_local);
   if (!inline_scan) {
     hipLaunchKernelGGL(perm_scan_kernel, dim3(E_local), dim3(256), 0, st, n_tiles, E_local, tile_counts, slot_total);
     err = hipGetLastError();

@@ -85,6 +85,19 @@ def test_permute_shapes(moe, T, E, k, E_local):
     _check(moe, idx, E, E_local, local, rng.integers(0, 65535, (T, 16)).astype(np.uint16))
 
 
+@pytest.mark.parametrize("T,E,k,E_local", [
+    (171, 24, 3, 10),         # 513 pairs: two tiles, one slot per load
+    (2040, 7, 2, 5), (2048, 7, 2, 5), (2049, 7, 2, 5),   # around 8 tiles: one and two rows of sums
+    (409 * 512, 12, 1, 10), (409 * 512 + 1, 12, 1, 10),  # one batch of single loads, and past it (scan launch)
+    (8 * 512, 520, 1, 511), (8 * 512 + 1, 520, 1, 513),  # widest rows of single loads, and past them
+    (2000, 8, 2, 8), (20000, 8, 2, 8),                   # few slots, four per load
+])
+def test_permute_inline_scan_edges(moe, T, E, k, E_local):
+    rng = np.random.default_rng(T + E_local)
+    idx = _rand_idx(rng, T, E, k)
+    _check(moe, idx, E, E_local, rng.permutation(E)[:E_local].astype(np.int32))
+
+
 def test_permute_degenerate(moe):
     rng = np.random.default_rng(1)
     T, E, k = 700, 16, 2
