@@ -98,6 +98,18 @@ def test_stats_configs(moe, name):
     np.testing.assert_array_equal(load, rl)
 
 
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 16384, 16385, 32768, 32769, 65536, 65537, 140000])
+def test_stats_batch_sizes(moe, n):
+    """One, two, four and eight pairs per thread, at the edges of each."""
+    rng = np.random.default_rng(n)
+    src = rng.integers(0, 3, n).astype(np.int32)
+    idx = rng.integers(0, 24, (n, 1)).astype(np.int32)
+    c, load = _stats(moe, src, idx, 3, 24)
+    oc, oload = oracle.route_stats(src, idx, 3, 24)
+    np.testing.assert_array_equal(c.cpu().numpy(), oc)
+    np.testing.assert_array_equal(load, oload)
+
+
 def test_stats_global_atomic_path_and_bad_ids(moe):
     """S*E beyond the LDS histogram (global atomics), and out-of-range source
     or expert ids, which are skipped: the expected counts are the oracle's over
