@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     constexpr int CPR = ROW / 16;            // 16-byte chunks per row
     constexpr int RPI = kWave / CPR;         // rows per load instruction
     constexpr int SWZ = 16 / CPR;            // rows sharing one swizzle key
-    constexpr int XPART = NSUB * 32 * ROW;   // token rows of one K part   // token rows of one K part
+    constexpr int XPART = NSUB * 32 * ROW;   // token rows of one K part
     constexpr int STAGE = NK * XPART + 4 * WB * 32 * ROW;
     constexpr int XL = NSUB * 32 / RPI / WN;// token loads per wave and stage
     constexpr int WL = WB * 32 / RPI;           // weight loads per wave and stage

@@ -15,6 +15,14 @@
 // groups that end at or before the tile.  Group sizes never leave the
 // device.
 //
+// Last round.  Where the tiles past the last whole round of the grid number
+// at most half the workgroups and half tiles are at hand (TAIL 2, one
+// problem), each is run as two tiles of 128 token rows on two CUs, dealt to
+// the XCDs in equal shares (in tile order they would fill one XCD after
+// another).  320 tiles of K 14336 on 256 CUs: 726 -> 642 us.  Dealing a last
+// round of whole tiles over the XCDs did not pay (DSV3 share layer, 4.75 and
+// 7.16 rounds, 2813 -> 2858 us; the selections cost registers too).
+//
 // Tail tiles.  An expert whose rows past its last whole m-tile number 1..128
 // takes them in tiles of 128 token rows, with their own LDS layout and
 // pipeline (see TAIL): half the MFMA work per row of a padded 256-row
@@ -265,7 +273,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int total_tiles = sp_tiles + ((TAIL && a.offsets != nullptr) ? total_mt : total_mt * n_tiles_n);
   const int per_xcd = gridDim.x / 8;
   const int first = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (first >= total_tiles) return;
+  // The last, partly filled round in halves (see "Last round" above): `item`
+  // is this workgroup's share of it, tile_end ends the workgroup's sequence.
+  const int n_wg = static_cast<int>(gridDim.x);
+  const int last = (TAIL == 2 && !PAIR) ? total_tiles / n_wg * n_wg : total_tiles;
+  const int items = 2 * (total_tiles - last);
+  const bool halves = items > 0 && items <= n_wg;
+  const int item = items * static_cast<int>(blockIdx.x % 8) / 8 + static_cast<int>(blockIdx.x / 8);
+  const int item_end = items * static_cast<int>(blockIdx.x % 8 + 1) / 8;
+  const int tile_end = !halves ? total_tiles : item < item_end ? last + n_wg : last;
+  if (first >= tile_end) return;
   const int sp_mt = sp_tiles > 0 ? ceil_div(sp.static_rows, kBM) : 1;
 
   struct TileInfo {
@@ -278,6 +295,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // and so are the buffer descriptors built from the tile (else the
     // compiler wraps each load in a loop over the lanes' descriptors)
     t_all = __builtin_amdgcn_readfirstlane(t_all);
+    const bool half = halves && t_all >= last;
+    if (half) t_all = last + (item >> 1);
     TileInfo ti;
     ti.tail = false;
     ti.p = (PAIR && t_all < sp_tiles) ? 0 : 1;
@@ -331,6 +350,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
           ti.tail = tl && r == fm;
           ti.nt = c;
           ti.m0 = r * kBM;
+          if (half) {  // (the second half of a tail tile has no rows)
+            ti.tail = true;
+            ti.m0 += (item & 1) * (kBM / 2);
+          }
         }
         ti.tail = __builtin_amdgcn_readfirstlane(ti.tail ? 1 : 0) != 0;
         ti.p = 1;
@@ -383,7 +406,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // the workgroup's current run of tiles of one kind: its first tile and the
   // first tile of its sequence past the run (loads past it are dead: no
   // traffic)
-  int run_start = first, run_end = total_tiles;
+  int run_start = first, run_end = tile_end;
   // (through ta: a selection between two captured references would index the
   // closure at run time and keep the kernel's arguments in scratch memory)
   auto prob = [&](int p) -> const GemmArgs& { return (!PAIR || p) ? ta.g : ta.sp; };
@@ -1000,7 +1023,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // With tail tiles a run also holds tiles of one problem only (the shared
   // problem's tiles come first and are never tails), so that its loads and
   // epilogue select no problem per tile.
-  for (int t = first; t < total_tiles;) {
+  for (int t = first; t < tile_end;) {
     const bool tail = TAIL && tile_info(t).tail;
     const bool shared = PAIR && t < sp_tiles;
     int e = t;
@@ -1008,9 +1031,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       if (shared)
         e = t + ceil_div(sp_tiles - t, static_cast<int>(gridDim.x)) * static_cast<int>(gridDim.x);
       else
-        while (e < total_tiles && tile_info(e).tail == tail) e += gridDim.x;
+        while (e < tile_end && tile_info(e).tail == tail) e += gridDim.x;
     } else {
-      e = total_tiles;
+      e = tile_end;
     }
     run_start = t;
     run_end = e;
@@ -1114,7 +1137,8 @@ hipError_t launch_tiled_t(const Segments& seg, const GemmArgs& g, const GemmArgs
                                        : ceil_div(seg.static_rows, kBM));
   const long long tiles = m_tiles * ceil_div(g.N, OUT_COLS) + ta.sp_tiles;
   if (tiles == 0) return hipSuccess;
-  long long grid = std::min<long long>(tiles, device_cu_count());  // one workgroup per CU (LDS)
+  // one workgroup per CU (LDS), up to two per tile (half tiles in the last round)
+  long long grid = std::min<long long>(2 * tiles, device_cu_count());
   grid = ((grid + 7) / 8) * 8;
   // group prefix values per lane: groups <= 64 * PFX
   if (seg.groups <= kWave) return launch_pfx<GATED, 1>(ta, grid, st);

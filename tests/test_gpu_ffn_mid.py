@@ -58,3 +58,9 @@ def test_tile_boundaries_on_the_tiled_kernel(moe, H, I):  # noqa: F811
 ])
 def test_decode_batches(moe, sizes, H, I, n_sh, I_sh):  # noqa: F811
     _sized(moe, sizes, H, I, n_sh, I_sh)
+
+
+def test_last_round_in_halves(moe):  # noqa: F811
+    """Gate/up on long K: 280 tiles, the 24 past the first 256 (whole tiles of
+    256 and 129 rows, and tail tiles, which have no second half) as halves."""
+    _sized(moe, [385] * 14 + [300, 128, 257, 385], 4104, 1016)
