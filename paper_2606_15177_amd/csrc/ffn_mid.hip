@@ -428,6 +428,9 @@ long long narrow_items(const Segments& seg, const GemmArgs& a, const GemmArgs* s
 // / 124 us; DSV3 share gate/up, 14 and 24 tokens (400, 610) 120 / 110 and 130
 // / 131 us; a stacked K of the shared experts (DSV2-Lite down, K 2816 among
 // 1408), 12 tokens (730) 38 / 31 us.
+// A deeper ring there (six stages in 160 KB, one workgroup per CU) does not
+// pay: Qwen3, 1 token, gate/up 14.6 -> 14.3 us but down 9.0 -> 10.7, and a layer
+// of four 139 -> 147 us, as each kernel waits for whole CUs' LDS.
 bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
   if (seg.max_rows > kWideRows) return false;
   const long long items = narrow_items(seg, a, sh, gated);

@@ -19,9 +19,9 @@
 // at most half the workgroups and half tiles are at hand (TAIL 2, one
 // problem), each is run as two tiles of 128 token rows on two CUs, dealt to
 // the XCDs in equal shares (in tile order they would fill one XCD after
-// another).  320 tiles of K 14336 on 256 CUs: 726 -> 642 us.  Dealing a last
-// round of whole tiles over the XCDs did not pay (DSV3 share layer, 4.75 and
-// 7.16 rounds, 2813 -> 2858 us; the selections cost registers too).
+// another).  320 tiles of K 14336 on 256 CUs: 726 -> 642 us.  Dealing longer
+// last rounds of whole tiles over the XCDs changed nothing (Mixtral 2000 tokens,
+// 8.75 rounds: layer 1545 and 1544 us; DSV3 share 3151 and 3147 us).
 //
 // Tail tiles.  An expert whose rows past its last whole m-tile number 1..128
 // takes them in tiles of 128 token rows, with their own LDS layout and
