@@ -42,7 +42,9 @@ bool skinny_ok(const GemmArgs& a);
 hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st);
 // Whether a batch of at most kSkinnyMaxRows tokens takes it.
 bool mid_streams(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated);
-hipError_t launch_tiled(const Segments& seg, const GemmArgs& a, bool gated, hipStream_t st);
+// Its launch: whether narrow items halve K, and its workgroups.
+bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated);
+long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated);
 
 // K from which the kernels count a product as long (see the rules that use it).
 constexpr int kLongK = 4096;

@@ -398,19 +398,12 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 template <bool GATED, int KP>
-hipError_t launch_mid_t(const Segments& seg, const GemmArgs& g, const GemmArgs& sp, hipStream_t st) {
-  constexpr int OUT_COLS = (GATED ? kMidCols / 2 : kMidCols) / KP;
+hipError_t launch_mid_t(long long blocks, const GemmArgs& g, const GemmArgs& sp, hipStream_t st) {
   static unsigned long long lds_set = 0;  // devices with the LDS limit raised
   const hipError_t e = set_max_dynamic_lds(reinterpret_cast<const void*>(&mid_kernel<GATED, KP>), kMidLds, &lds_set);
   if (e != hipSuccess) return e;
-  // at most one partly filled chunk per group; wide items need fewer column blocks
-  const long long chunks = seg.total_rows / kMidRows + std::min(seg.groups, seg.total_rows);
-  long long items = chunks * ceil_div(g.N, OUT_COLS);
-  if (sp.static_rows > 0) items += static_cast<long long>(ceil_div(sp.static_rows, kMidRows)) * ceil_div(sp.N, OUT_COLS);
-  const long long per_xcd = items / kXcds + 3;  // each kind's run rounds up by one
-  if (items == 0) return hipSuccess;
-  hipLaunchKernelGGL((mid_kernel<GATED, KP>), dim3(static_cast<unsigned>(per_xcd * kXcds)), dim3(kMidThreads), kMidLds,
-                     st, MidArgs{g, sp});
+  hipLaunchKernelGGL((mid_kernel<GATED, KP>), dim3(static_cast<unsigned>(blocks)), dim3(kMidThreads), kMidLds, st,
+                     MidArgs{g, sp});
   return hipGetLastError();
 }
 
@@ -419,6 +412,8 @@ long long narrow_items(const Segments& seg, const GemmArgs& a, const GemmArgs* s
   const int cols = gated ? kMidCols / 2 : kMidCols;
   return static_cast<long long>(seg.hit_groups) * ceil_div(a.N, cols) + (sh ? ceil_div(sh->N, cols) : 0);
 }
+
+}  // namespace
 
 // Few narrow items leave CUs idle and each runs through its whole K alone:
 // half as many columns and the K halves on two pairs of waves then.  Time
@@ -437,7 +432,14 @@ bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bo
   return items <= 128 || (a.K >= kLongK && items <= (gated ? 400 : 200)) || (sh && sh->K > a.K && items <= 768);
 }
 
-}  // namespace
+long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
+  const int cols = (gated ? kMidCols / 2 : kMidCols) / (mid_splits_k(seg, a, sh, gated) ? 2 : 1);
+  // at most one partly filled chunk per group; wide items need fewer column blocks
+  const long long chunks = seg.total_rows / kMidRows + std::min(seg.groups, seg.total_rows);
+  long long items = chunks * ceil_div(a.N, cols);
+  if (sh) items += static_cast<long long>(ceil_div(sh->static_rows, kMidRows)) * ceil_div(sh->N, cols);
+  return items == 0 ? 0 : (items / kXcds + 3) * kXcds;  // each kind's run on an XCD rounds up by one
+}
 
 // Batches of up to 64 tokens: everything but the gate/up projection of few,
 // wide experts, where the decode kernel's finer items still stream best
@@ -451,9 +453,11 @@ bool mid_streams(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, boo
 hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st) {
   const GemmArgs none{};
   const GemmArgs& sp = sh ? *sh : none;
+  const long long blocks = mid_blocks(seg, a, sh, gated);
+  if (blocks == 0) return hipSuccess;
   if (mid_splits_k(seg, a, sh, gated))
-    return gated ? launch_mid_t<true, 2>(seg, a, sp, st) : launch_mid_t<false, 2>(seg, a, sp, st);
-  return gated ? launch_mid_t<true, 1>(seg, a, sp, st) : launch_mid_t<false, 1>(seg, a, sp, st);
+    return gated ? launch_mid_t<true, 2>(blocks, a, sp, st) : launch_mid_t<false, 2>(blocks, a, sp, st);
+  return gated ? launch_mid_t<true, 1>(blocks, a, sp, st) : launch_mid_t<false, 1>(blocks, a, sp, st);
 }
 
 }  // namespace moe

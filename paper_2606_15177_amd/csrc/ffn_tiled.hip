@@ -1083,39 +1083,47 @@ hipError_t launch_pfx_t(const TiledArgs& ta, long long grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Grouped problems (device offsets) take the kernel with tail tiles; a
-// launch of static rows alone takes the blocked tile order.
-template <bool GATED, int PFX>
-hipError_t launch_pfx(const TiledArgs& ta, long long grid, hipStream_t st) {
-  if (ta.g.offsets == nullptr) {
-    if constexpr (PFX == 1) {
-      if (ta.sp_tiles == 0) return launch_pfx_t<GATED, 1, false, true, 0>(ta, grid, st);
-    }
-    return launch_pfx_t<GATED, PFX, true, false, 0>(ta, grid, st);
-  }
-  // (the tail variant with 16 prefix entries per lane, for more than 256
-  // groups, needs more registers than two waves per SIMD allow: there the
-  // tiles stay whole)
-  if constexpr (PFX > 4) {
-    return launch_pfx_t<GATED, PFX, true, false, 0>(ta, grid, st);
-  } else {
-    // with the shared experts' tiles in the launch: half tail tiles for the
-    // gated projection, whole tiles for the down projection (where tails
-    // lost to the whole tiles); alone: on long K half tail tiles, which keep
-    // pace with the full tiles of their weight rows, otherwise wide tail
-    // tiles, fewer of them (all measured)
-    if (ta.sp_tiles > 0) {
-      if constexpr (GATED) return launch_pfx_t<GATED, PFX, true, false, 2>(ta, grid, st);
-      else return launch_pfx_t<GATED, PFX, true, false, 0>(ta, grid, st);
-    }
-    if (ta.g.K >= kHalfTailK) return launch_pfx_t<GATED, PFX, false, false, 2>(ta, grid, st);
-    return launch_pfx_t<GATED, PFX, false, false, 1>(ta, grid, st);
-  }
+// Group prefix values per lane that a problem needs (groups <= 64 of them).
+int tiled_pfx(int groups) { return groups <= kWave ? 1 : groups <= 4 * kWave ? 4 : kMaxGroups / kWave; }
+
+// Tail tiles of a launch (see TAIL).  Grouped problems (not a launch of
+// static rows alone) take them; but the tail variant with 16 prefix entries
+// per lane, for more than 256 groups, needs more registers than two waves per
+// SIMD allow: there the tiles stay whole.  With the shared experts' tiles in
+// the launch: half tail tiles for the gated projection, whole tiles for the
+// down projection (where tails lost to the whole tiles); alone: on long K half
+// tail tiles, which keep pace with the full tiles of their weight rows,
+// otherwise wide tail tiles, fewer of them (all measured).
+int tiled_tail(const GemmArgs& g, bool with_shared, bool gated) {
+  if (g.static_rows > 0 || tiled_pfx(g.groups) > 4) return 0;
+  if (with_shared) return gated ? 2 : 0;
+  return g.K >= kHalfTailK ? 2 : 1;
 }
 
-// Host-side checks of one problem: at most kMaxGroups groups, and 32-bit byte offsets for a tile's X rows (all x_row_count rows
-// of x when rows are indexed), a group's weight columns and a tile's output
-// rows.
+// A launch of static rows alone takes the blocked tile order.
+template <bool GATED, int PFX>
+hipError_t launch_pfx(const TiledArgs& ta, long long grid, hipStream_t st) {
+  const bool shared = ta.sp_tiles > 0;
+  if constexpr (PFX == 1) {
+    if (ta.g.offsets == nullptr && !shared) return launch_pfx_t<GATED, 1, false, true, 0>(ta, grid, st);
+  }
+  if constexpr (PFX <= 4) {
+    switch (tiled_tail(ta.g, shared, GATED)) {
+      case 2:
+        if constexpr (GATED) {
+          if (shared) return launch_pfx_t<GATED, PFX, true, false, 2>(ta, grid, st);
+        }
+        return launch_pfx_t<GATED, PFX, false, false, 2>(ta, grid, st);
+      case 1: return launch_pfx_t<GATED, PFX, false, false, 1>(ta, grid, st);
+      default: break;
+    }
+  }
+  return launch_pfx_t<GATED, PFX, true, false, 0>(ta, grid, st);
+}
+
+// Host-side checks of one problem: at most kMaxGroups groups, and 32-bit byte
+// offsets for a tile's X rows (all x_row_count rows of x when rows are
+// indexed), a group's weight columns and a tile's output rows.
 bool tiled_ok(const Segments& seg, const GemmArgs& a) {
   if (seg.groups > kMaxGroups) return false;
   // grouped problems: tail tiles read 2 kBN weight rows, and only a single K segment
@@ -1127,23 +1135,32 @@ bool tiled_ok(const Segments& seg, const GemmArgs& a) {
   return x_span < 0x80000000ull && w_span < 0x80000000ull && o_span < 0x80000000ull;
 }
 
-// g over seg, after sp (static rows, sp_rows of them; 0: no second problem)
-template <bool GATED>
-hipError_t launch_tiled_t(const Segments& seg, const GemmArgs& g, const GemmArgs& sp, int sp_rows, hipStream_t st) {
-  constexpr int OUT_COLS = GATED ? kBN / 2 : kBN;
-  TiledArgs ta{g, sp, 0};
-  if (sp_rows > 0) ta.sp_tiles = ceil_div(sp_rows, kBM) * ceil_div(sp.N, OUT_COLS);
-  const long long m_tiles = (g.offsets ? static_cast<long long>(ceil_div(seg.total_rows, kBM)) + seg.groups
-                                       : ceil_div(seg.static_rows, kBM));
-  const long long tiles = m_tiles * ceil_div(g.N, OUT_COLS) + ta.sp_tiles;
-  if (tiles == 0) return hipSuccess;
+// Workgroups of a launch of g over seg, with sh's tiles before g's.
+long long tiled_blocks(const Segments& seg, const GemmArgs& g, const GemmArgs* sh, bool gated) {
+  const int out_cols = gated ? kBN / 2 : kBN;
+  const long long m_tiles = (g.static_rows > 0 ? ceil_div(seg.static_rows, kBM)
+                                               : static_cast<long long>(ceil_div(seg.total_rows, kBM)) + seg.groups);
+  long long tiles = m_tiles * ceil_div(g.N, out_cols);
+  if (sh) tiles += static_cast<long long>(ceil_div(sh->static_rows, kBM)) * ceil_div(sh->N, out_cols);
   // one workgroup per CU (LDS), up to two per tile (half tiles in the last round)
-  long long grid = std::min<long long>(2 * tiles, device_cu_count());
-  grid = ((grid + 7) / 8) * 8;
-  // group prefix values per lane: groups <= 64 * PFX
-  if (seg.groups <= kWave) return launch_pfx<GATED, 1>(ta, grid, st);
-  if (seg.groups <= 4 * kWave) return launch_pfx<GATED, 4>(ta, grid, st);
-  return launch_pfx<GATED, kMaxGroups / kWave>(ta, grid, st);
+  return (std::min<long long>(2 * tiles, device_cu_count()) + 7) / 8 * 8;
+}
+
+// g over seg, after sh (static rows; null: no second problem)
+hipError_t launch_tiled(const Segments& seg, const GemmArgs& g, const GemmArgs* sh, bool gated, hipStream_t st) {
+  if (!tiled_ok(seg, g)) return hipErrorInvalidValue;
+  const int out_cols = gated ? kBN / 2 : kBN;
+  TiledArgs ta{g, sh ? *sh : GemmArgs{}, 0};
+  if (sh) ta.sp_tiles = ceil_div(sh->static_rows, kBM) * ceil_div(sh->N, out_cols);
+  const long long grid = tiled_blocks(seg, g, sh, gated);
+  if (grid == 0) return hipSuccess;
+  switch (tiled_pfx(seg.groups)) {
+    case 1: return gated ? launch_pfx<true, 1>(ta, grid, st) : launch_pfx<false, 1>(ta, grid, st);
+    case 4: return gated ? launch_pfx<true, 4>(ta, grid, st) : launch_pfx<false, 4>(ta, grid, st);
+    default:
+      return gated ? launch_pfx<true, kMaxGroups / kWave>(ta, grid, st)
+                   : launch_pfx<false, kMaxGroups / kWave>(ta, grid, st);
+  }
 }
 
 GemmArgs up_gemm(const Segments& seg, const UpArgs& u) {
@@ -1217,38 +1234,63 @@ bool takes_mid(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, c
   return 3 * tiles < 2 * device_cu_count();
 }
 
-// One GEMM on its kernel, or two in one tiled launch when both take the
-// tiled kernel, the second has static rows and on its own it would leave a
-// partly filled last round of tiles: the routed tiles then fill it.  (When
-// the shared tiles fill whole rounds the one-problem kernel is faster: the
-// two-problem selections cost it about 2%.)
+// The launches of one GEMM, or of two: both in the mid-sized kernel, or in one
+// tiled launch when both take the tiled kernel, the second has static rows and
+// on its own it would leave a partly filled last round of tiles: the routed
+// tiles then fill it.  (When the shared tiles fill whole rounds the
+// one-problem kernel is faster: the two-problem selections cost it about 2%.)
+GemmPlan plan_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh, bool gated) {
+  GemmPlan p{};
+  const auto decode_blocks = [&](const Segments& s, const GemmArgs& q) {
+    return static_cast<long long>(ceil_div(q.N, gated ? 32 : 64)) * s.groups;
+  };
+  if (takes_mid(seg, a, sh_seg, sh, gated)) {
+    p.kernel = kFfnMid;
+    p.merged = sh != nullptr;
+    p.split_k = mid_splits_k(seg, a, sh, gated);
+    p.blocks = mid_blocks(seg, a, sh, gated);
+    return p;
+  }
+  const int out_cols = gated ? kBN / 2 : kBN;
+  p.kernel = ffn_streams_weights(seg) ? kFfnDecode : kFfnTiled;
+  p.merged = sh != nullptr && p.kernel == kFfnTiled && !ffn_streams_weights(*sh_seg) && sh->static_rows > 0 &&
+             static_cast<long long>(ceil_div(sh_seg->static_rows, kBM)) * ceil_div(sh->N, out_cols) %
+                     device_cu_count() != 0;
+  const GemmArgs* in = p.merged ? sh : nullptr;
+  p.tail = p.kernel == kFfnTiled ? tiled_tail(a, p.merged, gated) : 0;
+  p.blocks = p.kernel == kFfnTiled ? tiled_blocks(seg, a, in, gated) : decode_blocks(seg, a);
+  if (sh && !p.merged) {
+    p.sh_kernel = ffn_streams_weights(*sh_seg) ? kFfnDecode : kFfnTiled;
+    p.sh_blocks = p.sh_kernel == kFfnTiled ? tiled_blocks(*sh_seg, *sh, nullptr, gated) : decode_blocks(*sh_seg, *sh);
+  }
+  return p;
+}
+
 hipError_t launch_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh,
                         bool gated, hipStream_t st) {
-  const bool tiled = !ffn_streams_weights(seg);
-  if (takes_mid(seg, a, sh_seg, sh, gated)) return launch_mid(seg, a, sh, gated, st);
-  const int out_cols = gated ? kBN / 2 : kBN;
-  const bool merge = sh != nullptr && tiled && !ffn_streams_weights(*sh_seg) && sh_seg->offsets == nullptr &&
-                     static_cast<long long>(ceil_div(sh_seg->static_rows, kBM)) * ceil_div(sh->N, out_cols) %
-                             device_cu_count() != 0;
-  if (merge) {
-    if (!tiled_ok(seg, a) || !tiled_ok(*sh_seg, *sh)) return hipErrorInvalidValue;
-    return gated ? launch_tiled_t<true>(seg, a, *sh, sh_seg->static_rows, st)
-                 : launch_tiled_t<false>(seg, a, *sh, sh_seg->static_rows, st);
-  }
-  hipError_t e = tiled ? launch_tiled(seg, a, gated, st) : launch_skinny(seg, a, gated, st);
-  if (e != hipSuccess || sh == nullptr) return e;
-  return ffn_streams_weights(*sh_seg) ? launch_skinny(*sh_seg, *sh, gated, st) : launch_tiled(*sh_seg, *sh, gated, st);
+  const GemmPlan p = plan_gemm2(seg, a, sh_seg, sh, gated);
+  if (p.kernel == kFfnMid) return launch_mid(seg, a, sh, gated, st);
+  if (p.merged && !tiled_ok(*sh_seg, *sh)) return hipErrorInvalidValue;
+  hipError_t e = p.kernel == kFfnTiled ? launch_tiled(seg, a, p.merged ? sh : nullptr, gated, st)
+                                       : launch_skinny(seg, a, gated, st);
+  if (e != hipSuccess || sh == nullptr || p.merged) return e;
+  return p.sh_kernel == kFfnTiled ? launch_tiled(*sh_seg, *sh, nullptr, gated, st)
+                                  : launch_skinny(*sh_seg, *sh, gated, st);
 }
 
 }  // namespace
 
-hipError_t launch_tiled(const Segments& seg, const GemmArgs& a, bool gated, hipStream_t st) {
-  if (!tiled_ok(seg, a)) return hipErrorInvalidValue;
-  const GemmArgs none{};
-  return gated ? launch_tiled_t<true>(seg, a, none, 0, st) : launch_tiled_t<false>(seg, a, none, 0, st);
+bool ffn_streams_weights(const Segments& seg) { return seg.max_rows <= kSkinnyMaxRows; }
+
+GemmPlan plan_ffn_up(const Segments& seg, const UpArgs& u, const Segments* sh_seg, const UpArgs* sh) {
+  const GemmArgs s = sh ? up_gemm(*sh_seg, *sh) : GemmArgs{};
+  return plan_gemm2(seg, up_gemm(seg, u), sh_seg, sh ? &s : nullptr, true);
 }
 
-bool ffn_streams_weights(const Segments& seg) { return seg.max_rows <= kSkinnyMaxRows; }
+GemmPlan plan_ffn_down(const Segments& seg, const DownArgs& d, const Segments* sh_seg, const DownArgs* sh) {
+  const GemmArgs s = sh ? down_gemm(*sh_seg, *sh) : GemmArgs{};
+  return plan_gemm2(seg, down_gemm(seg, d), sh_seg, sh ? &s : nullptr, false);
+}
 
 bool ffn_up_supported(const Segments& seg, const UpArgs& u) { return up_ok(seg, u) && gemm_ok(seg, up_gemm(seg, u)); }
 

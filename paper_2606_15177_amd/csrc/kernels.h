@@ -111,6 +111,19 @@ hipError_t launch_ffn_up2(const Segments& seg, const UpArgs& a, const Segments& 
 // True for decode-sized groups (at most 64 rows each).
 bool ffn_streams_weights(const Segments& seg);
 
+// How one GEMM of the experts is launched (host only: the decisions that the
+// launchers take).
+enum FfnKernel { kFfnDecode = 0, kFfnMid = 1, kFfnTiled = 2 };
+struct GemmPlan {
+  int kernel;        // of the routed problem
+  int tail;          // tiled: its tail tiles (0 whole, 1 wide, 2 half)
+  bool split_k;      // mid: narrow items in two halves of K
+  bool merged;       // the shared experts in the same launch
+  long long blocks;  // workgroups of the routed launch
+  int sh_kernel;     // the shared experts' own launch (merged false)
+  long long sh_blocks;
+};
+
 // y[r][n] = sum_c h[r][c] Wd(g, n, c), h row stride K, y row stride N.
 // Wd(g, n, c) = w[g*group_stride + (c / kseg)*seg_stride + n*ldw + c % kseg]
 // (one segment per group for routed experts; the stacked shared experts use
@@ -123,6 +136,8 @@ struct DownArgs {
   size_t seg_stride, group_stride;
 };
 hipError_t launch_ffn_down(const Segments& seg, const DownArgs& a, hipStream_t st);
+GemmPlan plan_ffn_up(const Segments& seg, const UpArgs& a, const Segments* sh_seg, const UpArgs* sh);
+GemmPlan plan_ffn_down(const Segments& seg, const DownArgs& a, const Segments* sh_seg, const DownArgs* sh);
 // Host only: whether launch_ffn_down accepts these sizes (as above).
 bool ffn_down_supported(const Segments& seg, const DownArgs& a);
 hipError_t launch_ffn_down2(const Segments& seg, const DownArgs& a, const Segments& sh_seg, const DownArgs& sh,

@@ -223,8 +223,7 @@ int run_ffn(const moe_dims* d, const uint16_t* x_perm, const int32_t* x_rows, co
   const FfnPlan p = plan_ffn(d, x_perm, x_rows, x_rows != nullptr, offsets, w, x, y_perm, y_shared, ws);
   hipError_t e;
 
-  // routed and shared experts: one launch per GEMM when both take the tiled
-  // kernel, else one each
+  // routed and shared experts: in one launch per GEMM or one each (plan_gemm2)
   record(taps, 2 * MOE_STAGE_FFN_UP, st);
   if (d->n_shared > 0)
     e = moe::launch_ffn_up2(p.routed, p.up, p.shared, p.sh_up, st);
@@ -472,6 +471,26 @@ int moe_forward_noalloc(const moe_dims* d, const moe_gating* gating, const float
   // before it is read within the call
   return moe_forward(d, gating, logits, src, x, local_experts, w, counts, out, taps, ws,
                      MOE_NOALLOC_SCRATCH_BYTES, stream);
+}
+
+// For the tests, which assert the kernel that a shape is meant for (not part
+// of include/moe.h): how the expert GEMMs of these dims are launched by
+// moe_forward (rows_indexed) or moe_expert_ffn.  out[g] for g = 0 gate/up, 1
+// down: kernel, tail, split_k, merged, blocks, sh_kernel, sh_blocks.
+int moe_test_ffn_plan(const moe_dims* d, int rows_indexed, int64_t out[2][7]) {
+  const int s = check_dims(d);
+  if (s != MOE_OK) return s;
+  if (check_ffn_limits(d, rows_indexed != 0) != MOE_OK) return MOE_ERR_UNSUPPORTED;
+  const FfnPlan p = plan_ffn(d, nullptr, nullptr, rows_indexed != 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  const bool sh = d->n_shared > 0;
+  const moe::Segments* seg = sh ? &p.shared : nullptr;
+  const moe::GemmPlan g[2] = {moe::plan_ffn_up(p.routed, p.up, seg, sh ? &p.sh_up : nullptr),
+                              moe::plan_ffn_down(p.routed, p.dn, seg, sh ? &p.sh_dn : nullptr)};
+  for (int i = 0; i < 2; ++i) {
+    const int64_t v[7] = {g[i].kernel, g[i].tail, g[i].split_k, g[i].merged, g[i].blocks, g[i].sh_kernel, g[i].sh_blocks};
+    std::copy(v, v + 7, out[i]);
+  }
+  return MOE_OK;
 }
 
 size_t moe_place_slots(const moe_place_dims* pd, const int32_t* cap) {

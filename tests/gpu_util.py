@@ -124,3 +124,17 @@ def parallel_rows(fn, items):
     with cf.ThreadPoolExecutor(len(parts)) as ex:
         res = list(ex.map(fn, parts))
     return np.concatenate(res, axis=0)
+
+
+DECODE, MID, TILED = 0, 1, 2   # the expert GEMMs' kernels
+
+
+def ffn_plan(moe, d, rows_indexed: bool):
+    """(gate/up, down): how the layer's two expert GEMMs are launched by
+    moe_forward (rows_indexed) or moe_expert_ffn, as dicts."""
+    import ctypes as C
+    out = (C.c_int64 * 14)()
+    rc = moe._lib.moe_test_ffn_plan(C.byref(d), int(rows_indexed), out)
+    assert rc == moe.MOE_OK, rc
+    names = ("kernel", "tail", "split_k", "merged", "blocks", "sh_kernel", "sh_blocks")
+    return tuple(dict(zip(names, out[7 * g:7 * g + 7])) for g in (0, 1))
