@@ -271,17 +271,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
   // tiles of g: with TAIL the prefix already counts tiles
   const int total_tiles = sp_tiles + ((TAIL && a.offsets != nullptr) ? total_mt : total_mt * n_tiles_n);
-  const int per_xcd = gridDim.x / 8;
-  const int first = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int n_wg = static_cast<int>(gridDim.x);
+  const int xcd = static_cast<int>(blockIdx.x % 8), in_xcd = static_cast<int>(blockIdx.x / 8);
   // The last, partly filled round in halves (see "Last round" above): `item`
   // is this workgroup's share of it, tile_end ends the workgroup's sequence.
-  const int n_wg = static_cast<int>(gridDim.x);
   const int last = (TAIL == 2 && !PAIR) ? total_tiles / n_wg * n_wg : total_tiles;
   const int items = 2 * (total_tiles - last);
   const bool halves = items > 0 && items <= n_wg;
-  const int item = items * static_cast<int>(blockIdx.x % 8) / 8 + static_cast<int>(blockIdx.x / 8);
-  const int item_end = items * static_cast<int>(blockIdx.x % 8 + 1) / 8;
-  const int tile_end = !halves ? total_tiles : item < item_end ? last + n_wg : last;
+  const int item = items * xcd / 8 + in_xcd;
+  const int item_end = items * (xcd + 1) / 8;
+  // An only round too full for halves has fewer tiles than such a launch has
+  // workgroups: in equal shares per XCD too.
+  const bool one_round = TAIL == 2 && !PAIR && !halves && total_tiles < n_wg;
+  const int first = (one_round ? total_tiles * xcd / 8 : xcd * (n_wg / 8)) + in_xcd;
+  const int tile_end = one_round ? total_tiles * (xcd + 1) / 8
+                       : !halves ? total_tiles : item < item_end ? last + n_wg : last;
   if (first >= tile_end) return;
   const int sp_mt = sp_tiles > 0 ? ceil_div(sp.static_rows, kBM) : 1;
 
@@ -1142,8 +1146,13 @@ long long tiled_blocks(const Segments& seg, const GemmArgs& g, const GemmArgs* s
                                                : static_cast<long long>(ceil_div(seg.total_rows, kBM)) + seg.groups);
   long long tiles = m_tiles * ceil_div(g.N, out_cols);
   if (sh) tiles += static_cast<long long>(ceil_div(sh->static_rows, kBM)) * ceil_div(sh->N, out_cols);
-  // one workgroup per CU (LDS), up to two per tile (half tiles in the last round)
-  return (std::min<long long>(2 * tiles, device_cu_count()) + 7) / 8 * 8;
+  // One workgroup per CU (LDS); two per tile where the last round may run in
+  // halves.  Elsewhere a workgroup without a tile is not idle for free: the
+  // tiles go to the XCDs by workgroup, and twice the workgroups put them on
+  // half the XCDs (4 experts and a shared one, 900 tokens, H 8192, I 1024:
+  // layer 257 -> 278 us).
+  const bool halves = tiled_tail(g, sh != nullptr, gated) == 2 && !sh;
+  return (std::min<long long>(halves ? 2 * tiles : tiles, device_cu_count()) + 7) / 8 * 8;
 }
 
 // g over seg, after sh (static rows; null: no second problem)

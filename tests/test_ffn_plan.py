@@ -26,3 +26,25 @@ def _plan(moe, T, H, E, k, I, E_local=None, n_shared=0, I_shared=0, rows_indexed
 def test_kernels_of_the_workloads(moe, name, T, up, down):
     p = ffn_plan(moe, moe.dims_of(W.CONFIGS[name], T=T), True)
     assert [q["kernel"] for q in p] == [up, down]
+
+
+@pytest.mark.parametrize("dims,gemm,tiles", [
+    # the shared experts' tiles first (600 tokens: 3 m-tiles), then at most 7 routed m-tiles; gate/up, 4 column tiles
+    (dict(T=600, H=4096, E=4, k=1, I=512, n_shared=1, I_shared=512), 0, (3 + 7) * 4),
+    # down with whole tiles (shared rows), past the mid-sized kernel's mean: 4 + 3 + 8 m-tiles, one column tile
+    (dict(T=900, H=256, E=4, k=2, I=1024, n_shared=1, I_shared=1024), 1, 4 + 8 + 4),
+    # wide tail tiles: 32 + 10 m-tiles, 5 column tiles of 128
+    (dict(T=8000, H=1024, E=10, k=1, I=640), 0, (32 + 10) * 5),
+])
+def test_tiled_grid_is_one_workgroup_per_tile(moe, dims, gemm, tiles):
+    """The tiles are dealt to the XCDs by workgroup number: more workgroups
+    than tiles would leave whole XCDs without any."""
+    p = _plan(moe, **dims)[gemm]
+    assert p["kernel"] == TILED and (p["tail"] != 2 or p["merged"])
+    assert p["blocks"] == -(-min(tiles, 256) // 8) * 8
+
+
+def test_tiled_grid_two_workgroups_per_tile_for_halves(moe):
+    """Long K alone: the last round may run in half tiles, two workgroups each."""
+    p = _plan(moe, T=300, H=4096, E=3, k=1, I=512)[0]     # (2 + 3) x 4 tiles
+    assert (p["kernel"], p["tail"], p["merged"], p["blocks"]) == (TILED, 2, 0, 40)

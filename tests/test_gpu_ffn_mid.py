@@ -64,3 +64,9 @@ def test_last_round_in_halves(moe):  # noqa: F811
     """Gate/up on long K: 280 tiles, the 24 past the first 256 (whole tiles of
     256 and 129 rows, and tail tiles, which have no second half) as halves."""
     _sized(moe, [385] * 14 + [300, 128, 257, 385], 4104, 1016)
+
+
+def test_only_round_of_long_k(moe):  # noqa: F811
+    """Gate/up on long K, 200 tail tiles on 256 CUs: more than run in halves,
+    dealt to the XCDs in equal shares."""
+    _sized(moe, [41] * 20, 4104, 1160)
