@@ -19,8 +19,12 @@
 // at most half the workgroups and half tiles are at hand (TAIL 2, one
 // problem), each is run as two tiles of 128 token rows on two CUs, dealt to
 // the XCDs in equal shares (in tile order they would fill one XCD after
-// another).  320 tiles of K 14336 on 256 CUs: 726 -> 642 us.  Dealing longer
-// last rounds of whole tiles over the XCDs changed nothing (Mixtral 2000 tokens,
+// another).  320 tiles of K 14336 on 256 CUs: 726 -> 642 us.  The second half
+// of a tail tile has no rows and stores nothing, but it runs: it streams the
+// weight tile of the first half into the same L2, and a launch of tail tiles
+// alone is faster with it than without (Mixtral, evenly routed, 164, 256 and
+// 400 tokens: layer 628, 640 and 664 us with, 643, 657 and 693 without).
+// Dealing longer last rounds of whole tiles over the XCDs changed nothing (Mixtral 2000 tokens,
 // 8.75 rounds: layer 1545 and 1544 us; DSV3 share 3151 and 3147 us).
 //
 // Tail tiles.  An expert whose rows past its last whole m-tile number 1..128
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
           ti.tail = tl && r == fm;
           ti.nt = c;
           ti.m0 = r * kBM;
-          if (half) {  // (the second half of a tail tile has no rows)
+          if (half) {  // (the second half of a tail tile has no rows, see "Last round")
             ti.tail = true;
             ti.m0 += (item & 1) * (kBM / 2);
           }
