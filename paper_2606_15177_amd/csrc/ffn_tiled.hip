@@ -1062,23 +1062,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 }
 
-// Compute units of the current device, looked up once per device: a
-// per-device cache of a fixed property (atomic, so concurrent callers are
-// safe), sized for the devices one process can see.
-constexpr int kMaxDevices = 64;
-int device_cu_count() {
-  static int cus[kMaxDevices] = {};
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (dev >= 0 && dev < kMaxDevices) {
-    const int c = __atomic_load_n(&cus[dev], __ATOMIC_RELAXED);
-    if (c > 0) return c;
-  }
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-  if (dev >= 0 && dev < kMaxDevices) __atomic_store_n(&cus[dev], n, __ATOMIC_RELAXED);
-  return n;
-}
-
 template <bool GATED, int PFX, bool PAIR, bool SBLK, int TAIL>
 hipError_t launch_pfx_t(const TiledArgs& ta, long long grid, hipStream_t st) {
   static unsigned long long lds_set = 0;  // devices with the LDS limit raised
@@ -1292,6 +1275,23 @@ hipError_t launch_gemm2(const Segments& seg, const GemmArgs& a, const Segments* 
 }
 
 }  // namespace
+
+// Compute units of the current device, looked up once per device: a
+// per-device cache of a fixed property (atomic, so concurrent callers are
+// safe), sized for the devices one process can see.
+constexpr int kMaxDevices = 64;
+int device_cu_count() {
+  static int cus[kMaxDevices] = {};
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (dev >= 0 && dev < kMaxDevices) {
+    const int c = __atomic_load_n(&cus[dev], __ATOMIC_RELAXED);
+    if (c > 0) return c;
+  }
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  if (dev >= 0 && dev < kMaxDevices) __atomic_store_n(&cus[dev], n, __ATOMIC_RELAXED);
+  return n;
+}
 
 bool ffn_streams_weights(const Segments& seg) { return seg.max_rows <= kSkinnyMaxRows; }
 

@@ -111,6 +111,9 @@ hipError_t launch_ffn_up2(const Segments& seg, const UpArgs& a, const Segments& 
 // True for decode-sized groups (at most 64 rows each).
 bool ffn_streams_weights(const Segments& seg);
 
+// Compute units of the current device (256 without one).
+int device_cu_count();
+
 // How one GEMM of the experts is launched (host only: the decisions that the
 // launchers take).
 enum FfnKernel { kFfnDecode = 0, kFfnMid = 1, kFfnTiled = 2 };
@@ -169,6 +172,8 @@ struct PlaceArgs {
   double* cost;           // [L][3] or null
 };
 size_t place_lds_bytes(int S, int E, int G);
+// Host only: waves of a layer's workgroup.
+int place_waves(int L, int S, int E, int G);
 hipError_t launch_place(const PlaceArgs& a, hipStream_t st);
 
 // ---- window.hip ------------------------------------------------------------

@@ -493,6 +493,9 @@ int moe_test_ffn_plan(const moe_dims* d, int rows_indexed, int64_t out[2][7]) {
   return MOE_OK;
 }
 
+// For the tests: waves of a layer's workgroup in moe_place_experts.
+int moe_test_place_waves(int L, int S, int E, int G) { return moe::place_waves(L, S, E, G); }
+
 size_t moe_place_slots(const moe_place_dims* pd, const int32_t* cap) {
   if (pd == nullptr || cap == nullptr || pd->E < 1 || pd->G < 1) return 0;
   int slots = 0;

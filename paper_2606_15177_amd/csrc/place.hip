@@ -39,8 +39,7 @@
 namespace moe {
 namespace {
 
-constexpr int kPlaceThreads = 1024;
-constexpr int kPlaceWaves = kPlaceThreads / kWave;
+constexpr int kPlaceWaves = 16;  // of a layer's workgroup (WAVES below) at most, see place_waves
 
 struct PlaceKernelArgs {
   const int64_t* A;
@@ -68,14 +67,14 @@ struct PlaceLds {
   int32_t* xpos;   // [E] rank chosen for hotness position i
   int32_t* xs;     // [E] rank chosen for each expert
   int32_t* fill;   // [kPlaceMaxRanks] experts placed per rank
-  int64_t* red_i;  // [2 * kPlaceWaves]
+  int64_t* red_i;  // [2 * WAVES]
   double* A;       // [S*E] this layer's counts when they fit (a_staged), else
-                   // kPieceA values per wave: a piece of its experts' columns
+                   // piece_a values per wave: a piece of its experts' columns
 };
 
 // The layer's A is staged in LDS when it takes at most this many bytes.
 constexpr size_t kStageABytes = 32 * 1024;
-constexpr int kPieceA = static_cast<int>(kStageABytes / sizeof(double)) / kPlaceWaves;
+__host__ __device__ constexpr int piece_a(int waves) { return static_cast<int>(kStageABytes / sizeof(double)) / waves; }
 __host__ __device__ inline bool a_staged(int S, int E) {
   return static_cast<size_t>(S) * E * sizeof(int64_t) <= kStageABytes;
 }
@@ -90,8 +89,8 @@ __host__ __device__ inline int place_batch_experts(int G) {
 
 // Experts per chunk: at most 32, so that the first steps start early, and no
 // more than the waves beside wave 0 prepare in one batch each.
-__host__ __device__ inline int place_chunk_experts(int E, int G) {
-  int c = (kPlaceWaves - 1) * place_batch_experts(G);
+__host__ __device__ inline int place_chunk_experts(int E, int G, int waves) {
+  int c = (waves - 1) * place_batch_experts(G);
   c = c < 32 ? c : 32;
   return c < E ? c : E;
 }
@@ -99,7 +98,7 @@ __host__ __device__ inline int place_chunk_experts(int E, int G) {
 __host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~static_cast<size_t>(15); }
 
 // Byte offsets of the LDS carve; the same function sizes the launch.
-__host__ __device__ inline size_t place_lds_layout(int S, int E, int G, int chunk, size_t* off) {
+__host__ __device__ inline size_t place_lds_layout(int S, int E, int G, int chunk, int waves, size_t* off) {
   size_t o = 0;
   off[0] = o; o = align16(o + 16 * static_cast<size_t>(E));                 // bv
   off[1] = o; o = align16(o + sizeof(double) * S * G);                      // D
@@ -110,7 +109,7 @@ __host__ __device__ inline size_t place_lds_layout(int S, int E, int G, int chun
   off[6] = o; o = align16(o + sizeof(int32_t) * E);                         // xpos
   off[7] = o; o = align16(o + sizeof(int32_t) * E);                         // xs
   off[8] = o; o = align16(o + sizeof(int32_t) * kPlaceMaxRanks);            // fill
-  off[9] = o; o = align16(o + sizeof(int64_t) * 2 * kPlaceWaves);           // red_i
+  off[9] = o; o = align16(o + sizeof(int64_t) * 2 * waves);                 // red_i
   off[10] = o;
   o = align16(o + (a_staged(S, E) ? sizeof(double) * S * E : kStageABytes));  // A or its pieces
   return o;
@@ -160,16 +159,18 @@ __device__ __forceinline__ void wave_fence() {
 // One wave's share (experts w0, w0 + nw, ... in batches) of a chunk's terms.
 // A wave takes as many experts at once as fit its lanes beside their ranks
 // and, when A is not staged whole, as leave each a piece of its column.
+template <int WAVES>
 __device__ __forceinline__ void chunk_terms(const PlaceKernelArgs& a, const PlaceLds& s, int l, int c0, int nc,
                                             int t0, int w0, int nw, int wave, int lane, bool staged) {
+  constexpr int kPiece = piece_a(WAVES);
   const int S = a.S, E = a.E, G = a.G;
   const int64_t* A_l = a.A + static_cast<size_t>(l) * S * E;
   int per = place_batch_experts(G);
   const int gp = kWave / per;
   const int sub = lane / gp, g = lane % gp;
   if (!staged)
-    while (per > 1 && per * S > kPieceA) per /= 2;
-  double* own = s.A + wave * kPieceA;
+    while (per > 1 && per * S > kPiece) per /= 2;
+  double* own = s.A + wave * kPiece;
   auto expert_at = [&](int i) { return s.order[c0 + (i < nc ? i : nc - 1)]; };
   auto put = [&](int i, double comm) {
     if (sub < per && i < nc && g < G)
@@ -178,9 +179,9 @@ __device__ __forceinline__ void chunk_terms(const PlaceKernelArgs& a, const Plac
   if (staged) {
     for (int b = w0 * per; b < nc; b += nw * per)
       put(b + sub, comm_term(0.0, s.A + expert_at(b + sub), E, s.D + min(g, G - 1), S, G));
-  } else if (per * S <= kPieceA) {
+  } else if (per * S <= kPiece) {
     // the columns of several batches at once, so that their loads overlap
-    const int col = per * S, bats = kPieceA / col;
+    const int col = per * S, bats = kPiece / col;
     for (int b0 = w0 * per; b0 < nc; b0 += bats * nw * per) {
       const int nb = min(bats, ceil_div(nc - b0, nw * per));
 #pragma unroll 4
@@ -198,8 +199,8 @@ __device__ __forceinline__ void chunk_terms(const PlaceKernelArgs& a, const Plac
     // a column longer than the wave's piece (per == 1): piece by piece
     for (int b = w0; b < nc; b += nw) {
       double comm = 0.0;
-      for (int s0 = 0; s0 < S; s0 += kPieceA) {
-        const int n = min(kPieceA, S - s0);
+      for (int s0 = 0; s0 < S; s0 += kPiece) {
+        const int n = min(kPiece, S - s0);
 #pragma unroll 4
         for (int q = lane; q < n; q += kWave)
           own[q] = static_cast<double>(A_l[static_cast<size_t>(s0 + q) * E + expert_at(b)]);
@@ -341,7 +342,10 @@ __device__ __forceinline__ void place_chunk_steps(const PlaceKernelArgs& a, cons
   sc = sc + a.gamma * t.y;
   sc = placed < cap_g ? sc : inf;
   uint32_t won_steps = 0;  // bit i: this rank won step i
-#pragma unroll 2
+  // The loop at a fixed place in its cache lines: left where the code before it
+  // ends, the same loop takes up to 5% longer (48 layers of 128 experts on 8
+  // ranks 36.0 us so, 36.4 to 37.8 up to 28 bytes further on).
+  asm volatile(".p2align 6");
   for (int i = 0; i < nc; ++i) {
     const int i2 = min(i + 2, nc - 1);
     const double2 t2 = terms[i2 * G + gl];
@@ -413,7 +417,9 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a) {
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) void place_kernel(PlaceKernelArgs a) {
+  constexpr int kThreads = WAVES * kWave;
   extern __shared__ __align__(16) unsigned char place_smem[];
   const int l = blockIdx.x;
   const int tid = threadIdx.x;
@@ -424,7 +430,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
   const int32_t* x0_l = a.x0 + static_cast<size_t>(l) * E;
 
   size_t off[kLdsParts];
-  place_lds_layout(S, E, G, a.chunk, off);
+  place_lds_layout(S, E, G, a.chunk, WAVES, off);
   PlaceLds s;
   s.bv = reinterpret_cast<i64x2*>(place_smem + off[0]);
   s.D = reinterpret_cast<double*>(place_smem + off[1]);
@@ -442,7 +448,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
   // 1. hotness signals, D, and the layer's A when it fits in LDS
   int64_t part = 0;
   int negative = 0;
-  for (int e = tid; e < E; e += kPlaceThreads) {
+  for (int e = tid; e < E; e += kThreads) {
     int64_t v = 0;
 #pragma unroll 16
     for (int src = 0; src < S; ++src) {
@@ -458,18 +464,18 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
     part += b;
     negative |= static_cast<int>(b < 0);
   }
-  for (int i = tid; i < S * G; i += kPlaceThreads) s.D[i] = a.D[i];
+  for (int i = tid; i < S * G; i += kThreads) s.D[i] = a.D[i];
   part = wave_sum_i64(part);
   const int64_t neg_w = wave_sum_i64(negative);
   if (lane == 0) {
     s.red_i[wave] = part;
-    s.red_i[kPlaceWaves + wave] = neg_w;
+    s.red_i[WAVES + wave] = neg_w;
   }
   __syncthreads();
   int64_t total = 0, n_negative = 0;
-  for (int w = 0; w < kPlaceWaves; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     total += s.red_i[w];
-    n_negative += s.red_i[kPlaceWaves + w];
+    n_negative += s.red_i[WAVES + w];
   }
   // every expert is placed, so the final average rank load is known up front
   const double mean = static_cast<double>(total) / G;
@@ -480,8 +486,8 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
   // 2. hotness order: an expert's position is the number of experts ahead of
   // it; tpe consecutive lanes split the count of one expert
   int tpe = 1;
-  while (tpe < kWave && tpe * 2 * E <= kPlaceThreads) tpe *= 2;
-  for (int idx = tid; idx < E * tpe; idx += kPlaceThreads) {
+  while (tpe < kWave && tpe * 2 * E <= kThreads) tpe *= 2;
+  for (int idx = tid; idx < E * tpe; idx += kThreads) {
     const int e = idx / tpe;
     const int sub = idx - e * tpe;
     const i64x2 me = s.bv[e];
@@ -512,7 +518,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
   while ((1 << levels) < G) ++levels;
   // the first chunk's terms by all waves; then wave 0 places chunk after
   // chunk while the others prepare the next one
-  chunk_terms(a, s, l, 0, min(a.chunk, E), 0, wave, kPlaceWaves, wave, lane, staged);
+  chunk_terms<WAVES>(a, s, l, 0, min(a.chunk, E), 0, wave, WAVES, wave, lane, staged);
   __syncthreads();
   for (int c0 = 0, turn = 0; c0 < E; c0 += a.chunk, turn ^= 1) {
     const int nc = min(a.chunk, E - c0);
@@ -532,14 +538,14 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
       }
     } else if (c0 + a.chunk < E) {
       const int c1 = c0 + a.chunk;
-      chunk_terms(a, s, l, c1, min(a.chunk, E - c1), (turn ^ 1) * a.chunk * G, wave - 1, kPlaceWaves - 1, wave, lane, staged);
+      chunk_terms<WAVES>(a, s, l, c1, min(a.chunk, E - c1), (turn ^ 1) * a.chunk * G, wave - 1, WAVES - 1, wave, lane, staged);
     }
     __syncthreads();
   }
 
   // 4. results: the objective's terms from the ranks' sums, the placement by
   // expert, and each rank's experts in ascending order
-  for (int i = tid; i < E; i += kPlaceThreads) s.xs[s.order[i]] = s.xpos[i];
+  for (int i = tid; i < E; i += kThreads) s.xs[s.order[i]] = s.xpos[i];
   if (wave == 0) {
     if (lane < G) s.fill[lane] = r.placed;
     if (a.cost) {
@@ -555,7 +561,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
     }
   }
   __syncthreads();
-  for (int e = tid; e < E; e += kPlaceThreads) {
+  for (int e = tid; e < E; e += kThreads) {
     const int g = s.xs[e];
     a.x[static_cast<size_t>(l) * E + e] = g;
     if (a.rank_experts) {
@@ -572,7 +578,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
     }
   }
   if (a.rank_experts) {
-    for (int i = tid; i < G * a.slots; i += kPlaceThreads) {
+    for (int i = tid; i < G * a.slots; i += kThreads) {
       const int g = i / a.slots;
       if (i - g * a.slots >= s.fill[g])
         a.rank_experts[static_cast<size_t>(l) * G * a.slots + i] = -1;
@@ -582,10 +588,42 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceKernelArgs a)
 
 }  // namespace
 
-size_t place_lds_bytes(int S, int E, int G) {
+namespace {
+size_t place_lds_of(int S, int E, int G, int waves) {
   size_t off[kLdsParts];
-  return place_lds_layout(S, E, G, place_chunk_experts(E, G), off);
+  return place_lds_layout(S, E, G, place_chunk_experts(E, G, waves), waves, off);
 }
+}  // namespace
+
+size_t place_lds_bytes(int S, int E, int G) { return place_lds_of(S, E, G, kPlaceWaves); }
+
+// Waves per layer.  Sixteen waves, one workgroup per CU, place a layer
+// fastest; where the layers are more than the CUs, smaller workgroups share
+// the CUs and one round of them does more (16, 8 and 4 waves, us: 600 layers
+// of 64 experts on 8 ranks 59, 45 and 24; 300 of 128 on 8 70, 42 and 43; 200
+// 37, 37 and 39).  Counts not staged whole are fetched by the waves beside the
+// first all the time, which takes more of them (300 layers of 256 experts on
+// 32 ranks 157, 102 and 115; 200 sources, 8 ranks 498, 294 and 291).  Where
+// the LDS holds one workgroup anyway they gain nothing (64 sources and ranks
+// 204, 268 and 459).
+int place_waves(int L, int S, int E, int G) {
+  if (L <= device_cu_count()) return kPlaceWaves;
+  const int waves = a_staged(S, E) ? 4 : 8;
+  return 2 * place_lds_of(S, E, G, waves) <= static_cast<size_t>(kPlaceMaxLdsBytes) ? waves : kPlaceWaves;
+}
+
+namespace {
+template <int WAVES>
+hipError_t launch_place_t(const PlaceArgs& h, PlaceKernelArgs a, hipStream_t st) {
+  a.chunk = place_chunk_experts(h.E, h.G, WAVES);
+  const size_t lds = place_lds_of(h.S, h.E, h.G, WAVES);
+  static unsigned long long lds_set = 0;  // devices with the LDS limit raised
+  const hipError_t e_lds = set_max_dynamic_lds(reinterpret_cast<const void*>(&place_kernel<WAVES>), kPlaceMaxLdsBytes, &lds_set);
+  if (e_lds != hipSuccess) return e_lds;
+  hipLaunchKernelGGL(place_kernel<WAVES>, dim3(h.L), dim3(WAVES * kWave), lds, st, a);
+  return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_place(const PlaceArgs& h, hipStream_t st) {
   if (h.L == 0) return hipSuccess;
@@ -606,16 +644,12 @@ hipError_t launch_place(const PlaceArgs& h, hipStream_t st) {
   a.E = h.E;
   a.G = h.G;
   a.slots = h.slots;
-  a.chunk = place_chunk_experts(h.E, h.G);
   for (int g = 0; g < h.G; ++g) a.cap[g] = h.cap[g];
-  const size_t lds = place_lds_bytes(h.S, h.E, h.G);
-  static unsigned long long lds_set = 0;  // devices with the LDS limit raised
-  const hipError_t e_lds =
-      set_max_dynamic_lds(reinterpret_cast<const void*>(&place_kernel),
-                          kPlaceMaxLdsBytes, &lds_set);
-  if (e_lds != hipSuccess) return e_lds;
-  hipLaunchKernelGGL(place_kernel, dim3(h.L), dim3(kPlaceThreads), lds, st, a);
-  return hipGetLastError();
+  switch (place_waves(h.L, h.S, h.E, h.G)) {
+    case 4: return launch_place_t<4>(h, a, st);
+    case 8: return launch_place_t<8>(h, a, st);
+    default: return launch_place_t<kPlaceWaves>(h, a, st);
+  }
 }
 
 }  // namespace moe

@@ -157,6 +157,16 @@ def test_place_checks_alignment_and_noop(moe):
                                  None) == moe.MOE_OK
 
 
+@pytest.mark.parametrize("L,S,E,G,waves", [
+    (1, 8, 128, 8, 16), (256, 8, 128, 8, 16), (256, 64, 256, 64, 16),   # a CU for each layer
+    (257, 8, 128, 8, 4), (600, 8, 64, 8, 4),                            # layers share the CUs
+    (257, 32, 256, 32, 8), (600, 200, 256, 8, 8),                       # ... counts not staged whole
+    (257, 64, 256, 64, 16), (300, 4, 1024, 64, 16),                     # ... but the LDS holds one layer only
+])
+def test_place_workgroups_share_the_cus(moe, L, S, E, G, waves):
+    assert moe._lib.moe_test_place_waves(L, S, E, G) == waves
+
+
 @pytest.mark.parametrize("change,engine,code", [
     (dict(L=-1), False, -2), (dict(S=0), False, -2), (dict(E=0), False, -2), (dict(G=0, n_engines=0), False, -2),
     (dict(n_engines=0), True, -2),

@@ -36,6 +36,14 @@ def test_chunks_and_staging(moe, S, E, G):  # noqa: F811
     _check(moe, *_inputs(2, S, E, G, S + E + G), what=f"{S} {E} {G}")
 
 
+@pytest.mark.parametrize("S,E,G", [
+    (3, 33, 2), (8, 512, 8), (1, 70, 64),   # staged whole: four waves per layer
+    (100, 48, 3), (64, 70, 64), (300, 64, 5), (1100, 9, 3),   # columns and pieces: eight
+])
+def test_more_layers_than_cus(moe, S, E, G):  # noqa: F811
+    _check(moe, *_inputs(260, S, E, G, S + E + G), what=f"{S} {E} {G}")
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 @pytest.mark.parametrize("G", [2, 5, 8, 20])
 def test_bad_scores_beside_full_ranks(moe, G, bad):  # noqa: F811
