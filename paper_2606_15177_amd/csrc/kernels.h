@@ -47,6 +47,8 @@ hipError_t launch_route(int T, int E, int k, const float* logits, int32_t* topk_
 hipError_t launch_route_stats(int T, int k, int S, int E, const int32_t* src,
                               const int32_t* topk_idx, int64_t* counts, int32_t* expert_load,
                               hipStream_t st);
+// Host only: the pairs that a thread of it takes.
+int stats_per(int n_pairs, int S, int E);
 hipError_t launch_fill_i32(int32_t* p, int n, int32_t value, hipStream_t st);
 
 // ---- permute.hip -----------------------------------------------------------

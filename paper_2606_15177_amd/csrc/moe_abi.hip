@@ -493,6 +493,9 @@ int moe_test_ffn_plan(const moe_dims* d, int rows_indexed, int64_t out[2][7]) {
   return MOE_OK;
 }
 
+// For the tests: pairs per thread in moe_route_stats.
+int moe_test_stats_per(int n_pairs, int S, int E) { return moe::stats_per(n_pairs, S, E); }
+
 // For the tests: waves of a layer's workgroup in moe_place_experts.
 int moe_test_place_waves(int L, int S, int E, int G) { return moe::place_waves(L, S, E, G); }
 

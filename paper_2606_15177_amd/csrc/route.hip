@@ -28,6 +28,8 @@
 // holds few tokens, so each flushes about one global atomic per pair; the
 // layer's forward pass therefore counts in the dispatch's count pass, whose
 // blocks hold 512 pairs, whenever that pass runs.
+#include <algorithm>
+
 #include "common.h"
 #include "dispatch_impl.h"
 #include "kernels.h"
@@ -36,8 +38,7 @@ namespace moe {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kStatsBlocks = 64;    // blocks that the counting kernel spreads a batch over before they take more
-constexpr int kStatsPer = 8;        // pairs that a thread of it takes at most
+constexpr int kStatsPer = 8;        // pairs that a thread of the counting kernel takes at most
 
 __device__ __forceinline__ uint32_t order_key(float f) {
   if (f != f) return 0u;            // NaN: below every number
@@ -323,9 +324,7 @@ __global__ __launch_bounds__(kBlock) void route_kernel(RouteKernelArgs a) {
 }
 
 // Bound by the chain from a pair's loads to its block's flush: a thread takes
-// PER pairs whose loads go out together, one where that makes at most
-// kStatsBlocks blocks (more blocks flush more bins, with atomics on the same
-// counts).  2331 pairs: 6.8 us in two blocks of eight rounds, 3.0 us in ten.
+// PER pairs whose loads go out together (see stats_per).
 template <int PER>
 __global__ __launch_bounds__(kBlock) void stats_kernel(int n_pairs, int k, int S, int E,
                                                        const int32_t* __restrict__ src,
@@ -469,14 +468,29 @@ hipError_t launch_route(int T, int E, int k, const float* logits, int32_t* topk_
   return ext ? launch_route_ext<true>(a, st, dispatched) : launch_route_ext<false>(a, st, dispatched);
 }
 
+// Pairs per thread, as few as make at most `blocks` blocks.  Every block adds
+// its bins to the same counts: with some tens to thousands of bins the atomics
+// of 64 blocks take longer than the loads that they spread (one, two, four and
+// eight pairs per thread, with the fill before, us: 16384 pairs on 72 bins 7.2,
+// 5.3, 4.6 and 4.9, on 1024 12.3, 8.4, 6.3 and 5.8; 8192 pairs on 4096 bins
+// 13.4, 11.3, 8.9 and 7.2; 2331 on 72 3.8, 3.8, 4.1 and 4.5).  A few bins are
+// added faster than that (16384 pairs on 8 4.0, 3.8, 4.0 and 4.5), and a bin
+// per pair or no histogram at all leave as many atomics to any number of
+// blocks (16384 pairs on 16384 bins 12.4, 13.3, 14.0 and 14.4, on 65536 7.4,
+// 7.2, 7.6 and 8.7), until a block has more pairs than the loads in flight are
+// worth (65536 pairs on 16384 bins 25.0, 23.2, 20.3 and 17.1).
+int stats_per(int n_pairs, int S, int E) {
+  const long long bins = static_cast<long long>(S) * E;
+  const int blocks = bins > 16 && bins <= 8192 ? static_cast<int>(std::min(8LL, std::max(4LL, 16384 / bins))) : 64;
+  int per = 1;
+  while (per < kStatsPer && n_pairs > blocks * per * kBlock) per *= 2;
+  return per == 4 && bins > 8192 && bins <= kLdsBinsMax ? kStatsPer : per;
+}
+
 namespace {
 template <int PER>
 hipError_t launch_stats(int n_pairs, int k, int S, int E, const int32_t* src, const int32_t* topk_idx,
                         int64_t* counts, int32_t* expert_load, hipStream_t st) {
-  if constexpr (PER < kStatsPer) {
-    if (n_pairs > kStatsBlocks * PER * kBlock)
-      return launch_stats<2 * PER>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
-  }
   const int bins = (static_cast<long long>(S) * E <= kLdsBinsMax) ? S * E : 0;
   hipLaunchKernelGGL(stats_kernel<PER>, dim3(ceil_div(n_pairs, PER * kBlock)), dim3(kBlock), bins * sizeof(int), st,
                      n_pairs, k, S, E, src, topk_idx, reinterpret_cast<unsigned long long*>(counts), expert_load, bins);
@@ -489,7 +503,12 @@ hipError_t launch_route_stats(int T, int k, int S, int E, const int32_t* src,
                               hipStream_t st) {
   const int n_pairs = T * k;
   if (n_pairs == 0) return hipSuccess;
-  return launch_stats<1>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
+  switch (stats_per(n_pairs, S, E)) {
+    case 1: return launch_stats<1>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
+    case 2: return launch_stats<2>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
+    case 4: return launch_stats<4>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
+    default: return launch_stats<kStatsPer>(n_pairs, k, S, E, src, topk_idx, counts, expert_load, st);
+  }
 }
 
 hipError_t launch_fill_i32(int32_t* p, int n, int32_t value, hipStream_t st) {

@@ -157,6 +157,18 @@ def test_place_checks_alignment_and_noop(moe):
                                  None) == moe.MOE_OK
 
 
+@pytest.mark.parametrize("S,E,n,per", [
+    # few blocks where each adds its bins to the same counts
+    (3, 24, 2048, 1), (3, 24, 2049, 2), (8, 128, 4097, 4), (8, 128, 8193, 8), (8, 256, 65536, 8),
+    (32, 128, 4096, 4), (32, 128, 4097, 8),
+    # one bin per pair, no histogram at all, or a handful of bins: more of them
+    (64, 256, 16384, 1), (64, 256, 32768, 2), (64, 256, 32769, 8), (64, 1024, 16385, 2), (1, 8, 16384, 1), (1, 8, 65537, 8),
+    (1, 8, 2 ** 31 - 1, 8), (2, 2 ** 30, 1, 1),
+])
+def test_stats_blocks_by_bins(moe, S, E, n, per):
+    assert moe._lib.moe_test_stats_per(n, S, E) == per
+
+
 @pytest.mark.parametrize("L,S,E,G,waves", [
     (1, 8, 128, 8, 16), (256, 8, 128, 8, 16), (256, 64, 256, 64, 16),   # a CU for each layer
     (257, 8, 128, 8, 4), (600, 8, 64, 8, 4),                            # layers share the CUs

@@ -98,14 +98,17 @@ def test_stats_configs(moe, name):
     np.testing.assert_array_equal(load, rl)
 
 
-@pytest.mark.parametrize("n", [1, 255, 256, 257, 16384, 16385, 32768, 32769, 65536, 65537, 140000])
-def test_stats_batch_sizes(moe, n):
-    """One, two, four and eight pairs per thread, at the edges of each."""
+@pytest.mark.parametrize("S,E", [(3, 24), (2, 8), (65, 256)])
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385, 32768, 32769, 65536,
+                               65537, 140000])
+def test_stats_batch_sizes(moe, n, S, E):
+    """One, two, four and eight pairs per thread, at the edges of each (at 72
+    bins from 2048 pairs, at 16 and without a histogram from 16384)."""
     rng = np.random.default_rng(n)
-    src = rng.integers(0, 3, n).astype(np.int32)
-    idx = rng.integers(0, 24, (n, 1)).astype(np.int32)
-    c, load = _stats(moe, src, idx, 3, 24)
-    oc, oload = oracle.route_stats(src, idx, 3, 24)
+    src = rng.integers(0, S, n).astype(np.int32)
+    idx = rng.integers(0, E, (n, 1)).astype(np.int32)
+    c, load = _stats(moe, src, idx, S, E)
+    oc, oload = oracle.route_stats(src, idx, S, E)
     np.testing.assert_array_equal(c.cpu().numpy(), oc)
     np.testing.assert_array_equal(load, oload)
 
