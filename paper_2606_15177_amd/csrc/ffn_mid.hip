@@ -101,34 +101,51 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   // and chunk (fastest); an XCD owns an equal, contiguous run of each kind.
   const int sp_m = ma.sp.static_rows;
   const int sp_chunks = sp_m > 0 ? ceil_div(sp_m, kMidRows) : 0;
-  int n_wide = 0, n_narrow = 0;  // items of the routed groups
-  for (int gg = lane; gg < ma.g.groups; gg += kWave) {
-    const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
-    const int it = ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, 2 * FULL_COLS);
-    n_wide += n > kWideRows ? it : 0;
-    n_narrow += n > kWideRows ? 0 : it;
+  // Offset and rows of groups g0 + 64 i + lane, i < kPasses, their loads in
+  // flight together: up to 64 kPasses groups are read once, more in as many
+  // batches.  (64 groups at a time, and thrice over, a small batch of 1024
+  // experts spent most of its time here: H 512, I 256, 64 tokens, layer 117 us,
+  // 90 on the decode kernel.)
+  constexpr int kPasses = 4;
+  int first_row[kPasses], n_rows[kPasses];
+  auto load_groups = [&](int g0) {
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+      first_row[i] = n_rows[i] = 0;
+      if (g0 + i * kWave < ma.g.groups) {
+        const int gg = min(g0 + i * kWave + lane, ma.g.groups);  // past the last group: no rows
+        first_row[i] = ma.g.offsets[gg];
+        n_rows[i] = ma.g.offsets[min(gg + 1, ma.g.groups)];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) n_rows[i] -= first_row[i];
+  };
+  int c_wide = 0, c_narrow = 0;  // chunks of the routed groups
+  for (int g0 = 0; g0 < ma.g.groups; g0 += kPasses * kWave) {
+    load_groups(g0);
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+      c_wide += n_rows[i] > kWideRows ? ceil_div(n_rows[i], kMidRows) : 0;
+      c_narrow += n_rows[i] > 0 && n_rows[i] <= kWideRows ? 1 : 0;
+    }
   }
 #pragma unroll
   for (int off = 1; off < kWave; off <<= 1) {
-    n_wide += __shfl_xor(n_wide, off);
-    n_narrow += __shfl_xor(n_narrow, off);
+    c_wide += __shfl_xor(c_wide, off);
+    c_narrow += __shfl_xor(c_narrow, off);
   }
-  n_wide = __builtin_amdgcn_readfirstlane(n_wide);
-  n_narrow = __builtin_amdgcn_readfirstlane(n_narrow);
-  int n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, 2 * FULL_COLS) : 0;
+  c_wide = __builtin_amdgcn_readfirstlane(c_wide);
+  c_narrow = __builtin_amdgcn_readfirstlane(c_narrow);
+  const int narrow_blocks = ceil_div(ma.g.N, OUT_COLS);
+  const int n_narrow = c_narrow * narrow_blocks;
+  // items of the shared and of the wide groups where wide items cover `cols` output columns
+  auto shared_items = [&](int cols) { return sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, cols) : 0; };
   int wide_cols = 2 * FULL_COLS;
-  if (n_shared + n_wide < kFewWide) {
-    wide_cols = FULL_COLS;
-    n_shared = sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, wide_cols) : 0;
-    n_wide = 0;
-    for (int gg = lane; gg < ma.g.groups; gg += kWave) {
-      const int n = ma.g.offsets[gg + 1] - ma.g.offsets[gg];
-      n_wide += n > kWideRows ? ceil_div(n, kMidRows) * ceil_div(ma.g.N, wide_cols) : 0;
-    }
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) n_wide += __shfl_xor(n_wide, off);
-    n_wide = __builtin_amdgcn_readfirstlane(n_wide);
-  }
+  if (shared_items(wide_cols) + c_wide * ceil_div(ma.g.N, wide_cols) < kFewWide) wide_cols = FULL_COLS;
+  const int n_shared = shared_items(wide_cols);
+  const int wide_blocks = ceil_div(ma.g.N, wide_cols);
+  const int n_wide = c_wide * wide_blocks;
   const int xcd = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
   const int s_lo = run_start(n_shared, xcd), w_lo = run_start(n_wide, xcd), n_lo = run_start(n_narrow, xcd);
   const int my_shared = run_start(n_shared, xcd + 1) - s_lo;
@@ -152,29 +169,36 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   idx = narrow ? n_lo + idx : shared ? s_lo + idx : w_lo + idx - my_shared;
   int g = 0, row_base = 0, m = sp_m, item = idx;
   if (!shared) {
-    for (int g0 = 0;; g0 += kWave) {
-      const int gg = g0 + lane;
-      const int o0 = gg < ma.g.groups ? ma.g.offsets[gg] : 0;
-      const int n = gg < ma.g.groups ? ma.g.offsets[gg + 1] - o0 : 0;
-      const int own = (n > kWideRows) == wide ? ceil_div(n, kMidRows) * col_blocks(n, ma.g.N, OUT_COLS, wide_cols) : 0;
-      int inc = own;
+    // the group of the kind's chunk `at`, the kind's chunks before it in `before`
+    const int blocks = wide ? wide_blocks : narrow_blocks;
+    const int at = idx / blocks;
+    bool found = false;
+    for (int g0 = 0, before = 0; !found && g0 < ma.g.groups; g0 += kPasses * kWave) {
+      if (ma.g.groups > kPasses * kWave) load_groups(g0);
 #pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
+      for (int i = 0; i < kPasses; ++i) {
+        if (found || g0 + i * kWave >= ma.g.groups) continue;
+        const int own = (n_rows[i] > kWideRows) == wide ? ceil_div(n_rows[i], kMidRows) : 0;
+        int inc = own;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+          const int o = __shfl_up(inc, off);
+          if (lane >= off) inc += o;
+        }
+        const uint64_t past = __ballot(before + inc > at);
+        if (past) {
+          const int l = __ffsll(static_cast<long long>(past)) - 1;
+          g = g0 + i * kWave + l;
+          row_base = __builtin_amdgcn_readlane(first_row[i], l);
+          m = __builtin_amdgcn_readlane(n_rows[i], l);
+          item = idx - (before + __builtin_amdgcn_readlane(inc - own, l)) * blocks;
+          found = true;
+        } else {
+          before += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
       }
-      const uint64_t past = __ballot(inc > idx);
-      if (past) {
-        const int l = __ffsll(static_cast<long long>(past)) - 1;
-        g = g0 + l;
-        row_base = __builtin_amdgcn_readlane(o0, l);
-        m = __builtin_amdgcn_readlane(n, l);
-        item = idx - __builtin_amdgcn_readlane(inc - own, l);
-        break;
-      }
-      if (g0 + kWave >= ma.g.groups) return;  // not reached: idx lies within the groups' items
-      idx -= __builtin_amdgcn_readlane(inc, kWave - 1);
     }
+    if (!found) return;  // not reached: idx lies within the groups' items
   }
   const int n_chunks = ceil_div(m, kMidRows);
   int nblk = item / n_chunks;

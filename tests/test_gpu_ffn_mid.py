@@ -70,3 +70,10 @@ def test_only_round_of_long_k(moe):  # noqa: F811
     """Gate/up on long K, 200 tail tiles on 256 CUs: more than run in halves,
     dealt to the XCDs in equal shares."""
     _sized(moe, [41] * 20, 4104, 1160)
+
+
+@pytest.mark.parametrize("sizes", [[1] * 256, [0] * 255 + [5], [0] * 256 + [70], [2] * 257 + [66, 0], [65] + [0] * 320 + [3],
+                                   [0] * 1023 + [3], [1] * 40 + [0] * 943 + [130] + [1] * 40])
+def test_many_groups(moe, sizes):  # noqa: F811
+    """The group of an item, at and past 256 groups (one batch of offsets)."""
+    _sized(moe, sizes, 72, 136)
