@@ -7,8 +7,10 @@
 // one group (a chunk) times a block of weight rows.  Groups of up to 64 rows
 // take narrow items of 128 weight rows, larger groups wide ones of 256 (of
 // 128 where a launch has few wide items, which would otherwise run on long
-// after the rest: Mixtral down at 100 tokens 318 -> 223 us, DSV2-Lite down at
-// 200 tokens 97 -> 71 us).  A wave owns 32-row blocks of the weights (gate/up:
+// after the rest, one to a CU: Mixtral down at 100 tokens 318 -> 223 us,
+// DSV2-Lite down at 200 tokens 97 -> 71 us; with the line at 128, 17 experts of H
+// 2208, I 1064 and a shared one of 1392, 642 tokens, layer 153 us, 116 at 256;
+// at 384 as many layers lose as win).  A wave owns 32-row blocks of the weights (gate/up:
 // 16 gate rows and the 16 up rows of the same columns, which the MFMA's C
 // layout puts into one lane) and all token rows of the chunk.  Dispatched as
 // plain workgroups, two per CU: a persistent grid over 256-row tiles left CUs
@@ -54,7 +56,7 @@ namespace {
 constexpr int kMidRows = 128;        // token rows of a chunk
 constexpr int kWideRows = 64;        // groups of more rows take wide items
 constexpr int kMidCols = 128;        // weight rows of a narrow item
-constexpr int kFewWide = 128;        // fewer wide items than this take 128 weight rows: half the CUs' worth
+constexpr int kFewWide = 256;        // fewer wide items than this (one per CU) take 128 weight rows
 constexpr int kMidThreads = 4 * kWave;
 constexpr int kMidLds = 80 * 1024;   // two workgroups per CU
 constexpr int kXcds = 8;
