@@ -37,6 +37,10 @@ hipError_t launch_skinny(const Segments& seg, const GemmArgs& a, bool gated, hip
 // Host-side size limits of the weight-streaming kernel (launch_skinny
 // refuses arguments that fail this check).
 bool skinny_ok(const GemmArgs& a);
+// Its workgroups: 32 output columns of a group each (gated), or 64.
+inline long long skinny_blocks(const Segments& seg, const GemmArgs& a, bool gated) {
+  return static_cast<long long>(ceil_div(a.N, gated ? 32 : 64)) * seg.groups;
+}
 // The mid-sized kernel: seg with device offsets, sh (nullable) with static
 // rows in the same launch; the caller has checked both (tiled_ok).
 hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st);

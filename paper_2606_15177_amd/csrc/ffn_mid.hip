@@ -441,6 +441,11 @@ long long narrow_items(const Segments& seg, const GemmArgs& a, const GemmArgs* s
 
 }  // namespace
 
+// Whether narrow_items is close: where not all experts are hit, skewed routing
+// hits fewer still (24 tokens, top 8 of 96 experts, Zipf 1, 24 of them, gate/up
+// of 210 items by even routing: 48 us with K in halves, 59 without).
+bool mostly_hit(const Segments& seg) { return 20 * seg.hit_groups >= 19 * seg.groups; }
+
 // Few narrow items leave CUs idle and each runs through its whole K alone:
 // half as many columns and the K halves on two pairs of waves then.  Time
 // without / with the split: Qwen3, 1 token (96 and 128 items) gate/up 18.0 /
@@ -448,14 +453,18 @@ long long narrow_items(const Segments& seg, const GemmArgs& a, const GemmArgs* s
 // Mixtral down, 1, 4 and 8 tokens (70, 175, 230) 83.6 / 59.0, 96 / 80 and 112
 // / 124 us; DSV3 share gate/up, 14 and 24 tokens (400, 610) 120 / 110 and 130
 // / 131 us; a stacked K of the shared experts (DSV2-Lite down, K 2816 among
-// 1408), 12 tokens (730) 38 / 31 us.
+// 1408), 12 tokens (730) 38 / 31 us.  Not on long K of gate/up alone with a few
+// more items than half the CUs over mostly hit experts (8 experts of H 4096, 24 and 64 tokens: I
+// 1408, 176 items, 58 / 60 and 64 / 74 us; 4 of H 8192, I 5632, 352 items 227 /
+// 213 and 235 / 244).
 // A deeper ring there (six stages in 160 KB, one workgroup per CU) does not
 // pay: Qwen3, 1 token, gate/up 14.6 -> 14.3 us but down 9.0 -> 10.7, and a layer
 // of four 139 -> 147 us, as each kernel waits for whole CUs' LDS.
 bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
   if (seg.max_rows > kWideRows) return false;
   const long long items = narrow_items(seg, a, sh, gated);
-  return items <= 128 || (a.K >= kLongK && items <= (gated ? 400 : 200)) || (sh && sh->K > a.K && items <= 768);
+  return items <= 128 || (a.K >= kLongK && items <= (gated ? 400 : 200) && !(gated && !sh && items <= 220 && mostly_hit(seg))) ||
+         (sh && sh->K > a.K && items <= 768);
 }
 
 long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
@@ -467,13 +476,25 @@ long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh,
   return items == 0 ? 0 : (items / kXcds + 3) * kXcds;  // each kind's run on an XCD rounds up by one
 }
 
-// Batches of up to 64 tokens: everything but the gate/up projection of few,
-// wide experts, where the decode kernel's finer items still stream best
-// (Mixtral, time of this kernel over that one's: 1.02 at 8 to 24 tokens, 1.00
-// to 1.02 at 40 to 64, where the rest of the range is 0.6 to 1.0: Qwen3 gate/up
-// 0.99 at 64, DSV2-Lite 0.60 at 1 and 0.85 at 40, DSV3 share 0.81 at 64).
+// Batches of up to 64 tokens: everything but two kinds of launch without
+// shared rows, where the decode kernel's finer items, four K parts each, are
+// faster (times of its and of this kernel, us, in layers of 2 of E experts).
+//   Small ones, a few rows per expert, K up to 1024 and all its workgroups on
+//   the CUs at once: it knows its rows without a search over the groups (H
+//   1280, I 448, 8 experts, one token, top 3: layer 20 and 21.5).
+//   Gate/up of many items over mostly hit experts (E 8, H 4096, 24 and 64
+//   tokens: I 2816 112 and 126, 118 and 134; E 16, H 2048, I 2816, 48 tokens 104
+//   and 109; 64 experts of H 2048, I 768, top 8, 45 tokens 130 and 138); not on
+//   K of 8192 (E 16, I 2816, 64 tokens 410 and 388) unless there are very many
+//   (Mixtral, 1.02 at 8 to 24 tokens, 1.00 to 1.02 at 40 to 64), nor with fewer
+//   items (E 8, H 4096, I 1408, 24 tokens 64 and 58).
 bool mid_streams(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
-  return !(gated && !sh && a.K >= kLongK && narrow_items(seg, a, sh, gated) >= 1024);
+  if (sh) return true;
+  if (a.K <= 1024 && seg.mean_rows <= 8 && skinny_blocks(seg, a, gated) <= device_cu_count()) return false;
+  if (!gated) return true;
+  const long long items = narrow_items(seg, a, sh, gated);
+  if (a.K >= kLongK && items >= 1024) return false;
+  return !(mostly_hit(seg) && a.K < 2 * kLongK && items >= (a.K >= kLongK ? 300 : 600));
 }
 
 hipError_t launch_mid(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated, hipStream_t st) {

@@ -1237,9 +1237,6 @@ bool takes_mid(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, c
 // one-problem kernel is faster: the two-problem selections cost it about 2%.)
 GemmPlan plan_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh, bool gated) {
   GemmPlan p{};
-  const auto decode_blocks = [&](const Segments& s, const GemmArgs& q) {
-    return static_cast<long long>(ceil_div(q.N, gated ? 32 : 64)) * s.groups;
-  };
   if (takes_mid(seg, a, sh_seg, sh, gated)) {
     p.kernel = kFfnMid;
     p.merged = sh != nullptr;
@@ -1254,10 +1251,10 @@ GemmPlan plan_gemm2(const Segments& seg, const GemmArgs& a, const Segments* sh_s
                      device_cu_count() != 0;
   const GemmArgs* in = p.merged ? sh : nullptr;
   p.tail = p.kernel == kFfnTiled ? tiled_tail(a, p.merged, gated) : 0;
-  p.blocks = p.kernel == kFfnTiled ? tiled_blocks(seg, a, in, gated) : decode_blocks(seg, a);
+  p.blocks = p.kernel == kFfnTiled ? tiled_blocks(seg, a, in, gated) : skinny_blocks(seg, a, gated);
   if (sh && !p.merged) {
     p.sh_kernel = ffn_streams_weights(*sh_seg) ? kFfnDecode : kFfnTiled;
-    p.sh_blocks = p.sh_kernel == kFfnTiled ? tiled_blocks(*sh_seg, *sh, nullptr, gated) : decode_blocks(*sh_seg, *sh);
+    p.sh_blocks = p.sh_kernel == kFfnTiled ? tiled_blocks(*sh_seg, *sh, nullptr, gated) : skinny_blocks(*sh_seg, *sh, gated);
   }
   return p;
 }

@@ -48,3 +48,24 @@ def test_tiled_grid_two_workgroups_per_tile_for_halves(moe):
     """Long K alone: the last round may run in half tiles, two workgroups each."""
     p = _plan(moe, T=300, H=4096, E=3, k=1, I=512)[0]     # (2 + 3) x 4 tiles
     assert (p["kernel"], p["tail"], p["merged"], p["blocks"]) == (TILED, 2, 0, 40)
+
+
+@pytest.mark.parametrize("dims,up,down", [
+    # small decode batches of short K; gate/up of many items over hit experts
+    (dict(T=1, H=1280, E=8, k=3, I=448), MID, DECODE),
+    (dict(T=1, H=640, E=8, k=3, I=448), DECODE, DECODE),
+    (dict(T=1, H=640, E=8, k=3, I=448, n_shared=1, I_shared=448), MID, MID),
+    (dict(T=64, H=640, E=8, k=3, I=448), MID, MID),
+    (dict(T=24, H=4096, E=8, k=2, I=2816), DECODE, MID),
+    (dict(T=8, H=2048, E=16, k=2, I=5632), MID, MID),        # a third of the experts not hit
+    (dict(T=24, H=8192, E=16, k=2, I=2816), MID, MID),
+])
+def test_kernels_by_rule(moe, dims, up, down):
+    assert [q["kernel"] for q in _plan(moe, **dims)] == [up, down]
+
+
+def test_long_k_split_by_items(moe):
+    """Gate/up of 8 hit experts on K 4096: 176 items run whole, few in halves."""
+    assert _plan(moe, T=64, H=4096, E=8, k=2, I=1408)[0]["split_k"] == 0
+    assert _plan(moe, T=64, H=4096, E=8, k=2, I=704)[0]["split_k"] == 1
+    assert _plan(moe, T=24, H=5120, E=96, k=8, I=640, E_local=24)[0]["split_k"] == 1   # not mostly hit
