@@ -51,6 +51,13 @@ def test_tiled_grid_two_workgroups_per_tile_for_halves(moe):
 
 
 @pytest.mark.parametrize("dims,up,down", [
+    # tiles of more than half a round, or of several: gate/up on them
+    (dict(T=824, H=1560, E=36, k=7, I=1496, E_local=31, n_shared=1, I_shared=1024), TILED, MID),
+    (dict(T=3143, H=2688, E=48, k=2, I=2048), TILED, TILED),
+    # ... of at most half a round, of few rows, of a short K
+    (dict(T=600, H=2048, E=8, k=2, I=512), MID, MID),
+    (dict(T=400, H=2688, E=48, k=2, I=3200), MID, MID),
+    (dict(T=3143, H=896, E=48, k=2, I=3200), MID, TILED),
     # small decode batches of short K; gate/up of many items over hit experts
     (dict(T=1, H=1280, E=8, k=3, I=448), MID, DECODE),
     (dict(T=1, H=640, E=8, k=3, I=448), DECODE, DECODE),
