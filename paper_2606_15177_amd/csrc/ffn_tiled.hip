@@ -1213,17 +1213,17 @@ bool gemm_ok(const Segments& seg, const GemmArgs& a) {
 // a round of tiles is the shorter one unless most of its rows are padding or
 // its K is short.  The mid-sized kernel is kept where the tiles fill at most
 // half a round; where the mean rows over all weight rows (the shared ones
-// included) are at most 100, or 125 past the first round; and on K up to 1000.
+// included) are at most 125, or 200 past the second round; and on K up to 1000.
 // Over 2300 layers of random sizes (E 4 to 256, H 64 to 8192, I 64 to 12800, 65
 // to 4096 tokens, popularity of the experts from even to Zipf 1.2) this leaves
-// 28 that take more than 1.05 times as long as on tiles alone, 69 without it
+// 31 that take more than 1.05 times as long as on tiles alone, 69 without it
 // (H 1560, I 1496, 31 of 36 experts, 824 tokens: 265 us, 220 so), at 0.80 of
 // their time on average.
 bool mid_up_wins(const Segments& seg, const GemmArgs& a, const GemmArgs* sh) {
   if (a.K <= 1000) return true;
   const double w = static_cast<double>(seg.groups) * a.N, s = sh ? sh->N : 0;
   const double mean = (seg.mean_rows * w + (sh ? sh->static_rows : 0) * s) / (w + s);
-  if (mean <= 100) return true;
+  if (mean <= 125) return true;
   // a group's m-tiles on average: its rows, half a tail tile (0.58 of a whole
   // one beside shared rows) where there are few
   const double m_tiles = std::max(sh ? 0.58 : 0.5, seg.mean_rows / static_cast<double>(kBM) + 0.25);
@@ -1231,7 +1231,7 @@ bool mid_up_wins(const Segments& seg, const GemmArgs& a, const GemmArgs* sh) {
   const double tiles = seg.groups * m_tiles * ceil_div(a.N, out_cols) +
                        (sh ? static_cast<double>(ceil_div(sh->static_rows, kBM)) * ceil_div(sh->N, out_cols) : 0.0);
   const double rounds = tiles / device_cu_count();
-  return rounds <= 0.5 || (rounds > 1 && mean <= 125);
+  return rounds <= 0.5 || (rounds > 2 && mean <= 200);
 }
 
 // Whether a grouped problem takes the mid-sized kernel (ffn_mid.hip) rather

@@ -53,7 +53,8 @@ def test_tiled_grid_two_workgroups_per_tile_for_halves(moe):
 @pytest.mark.parametrize("dims,up,down", [
     # tiles of more than half a round, or of several: gate/up on them
     (dict(T=824, H=1560, E=36, k=7, I=1496, E_local=31, n_shared=1, I_shared=1024), TILED, MID),
-    (dict(T=3143, H=2688, E=48, k=2, I=2048), TILED, TILED),
+    (dict(T=3143, H=2688, E=48, k=2, I=1400), TILED, TILED),
+    (dict(T=2211, H=2048, E=128, k=8, I=768), MID, TILED),    # (past the second round, a mean of 138)
     # ... of at most half a round, of few rows, of a short K
     (dict(T=600, H=2048, E=8, k=2, I=512), MID, MID),
     (dict(T=400, H=2688, E=48, k=2, I=3200), MID, MID),
