@@ -49,6 +49,8 @@ bool mid_streams(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, boo
 // Its launch: whether narrow items halve K, and its workgroups.
 bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated);
 long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated);
+constexpr int kMidThreads = 4 * kWave;
+constexpr long long kMidMaxBlocks = 0xffffffffll / kMidThreads;  // a grid dimension holds 2^32 - 1 threads
 
 // K from which the kernels count a product as long (see the rules that use it).
 constexpr int kLongK = 4096;

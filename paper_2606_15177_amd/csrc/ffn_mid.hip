@@ -57,7 +57,6 @@ constexpr int kMidRows = 128;        // token rows of a chunk
 constexpr int kWideRows = 64;        // groups of more rows take wide items
 constexpr int kMidCols = 128;        // weight rows of a narrow item
 constexpr int kFewWide = 256;        // fewer wide items than this (one per CU) take 128 weight rows
-constexpr int kMidThreads = 4 * kWave;
 constexpr int kMidLds = 80 * 1024;   // two workgroups per CU
 constexpr int kXcds = 8;
 constexpr int kTurn = 8;             // items per turn: a multiple of an XCD's shader engines

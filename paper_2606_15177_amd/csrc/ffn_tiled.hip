@@ -1238,8 +1238,10 @@ bool mid_up_wins(const Segments& seg, const GemmArgs& a, const GemmArgs* sh) {
 // than 256-row tiles or, in decode batches, the decode kernel; `sh` joins it.
 bool takes_mid(const Segments& seg, const GemmArgs& a, const Segments* sh_seg, const GemmArgs* sh, bool gated) {
   if (a.static_rows > 0 || (sh && sh->static_rows == 0)) return false;
-  // 32-bit offsets (the decode kernel accepts larger ones)
+  // 32-bit offsets (the decode kernel accepts larger ones), and one launch's
+  // number of threads (all items in one dimension)
   if (!tiled_ok(seg, a) || (sh && !tiled_ok(*sh_seg, *sh))) return false;
+  if (mid_blocks(seg, a, sh, gated) > kMidMaxBlocks) return false;
   if (ffn_streams_weights(seg)) return mid_streams(seg, a, sh, gated);
   if (gated && a.K < kHalfTailK && !mid_up_wins(seg, a, sh)) return false;
   if (seg.mean_rows <= kMidMean) return true;

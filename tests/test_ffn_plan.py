@@ -77,3 +77,13 @@ def test_long_k_split_by_items(moe):
     assert _plan(moe, T=64, H=4096, E=8, k=2, I=1408)[0]["split_k"] == 0
     assert _plan(moe, T=64, H=4096, E=8, k=2, I=704)[0]["split_k"] == 1
     assert _plan(moe, T=24, H=5120, E=96, k=8, I=640, E_local=24)[0]["split_k"] == 1   # not mostly hit
+
+
+def test_mid_launch_fits_one_grid_dimension(moe):
+    """1024 experts of 2^21 output columns make more items than one grid
+    dimension holds threads for (2^32 - 1): the decode kernel's grid has two."""
+    d = moe.dims(64, 2 ** 21, 1024, 32, 8, 2, 1024)
+    assert moe.validate(d, moe.ENTRY_EXPERT_FFN, 1 << 62) == moe.MOE_OK
+    assert ffn_plan(moe, d, False)[1]["kernel"] == DECODE
+    p = _plan(moe, T=64, H=2 ** 20, E=1024, k=32, I=8, rows_indexed=False)[1]
+    assert p["kernel"] == MID and p["blocks"] * 256 < 2 ** 32
