@@ -1,6 +1,7 @@
-"""GPU parity of the expert FFN grouped GEMMs (weight-streaming path for
-decode-sized batches, LDS-tiled MFMA path for larger ones) and of the combine
-kernel against the CPU oracle."""
+"""GPU parity of the expert FFN grouped GEMMs (whichever kernel the launch rules
+give a shape: the mid-sized kernel for most of these, the decode kernel for small
+launches, 256-row tiles for long K or many rows) and of the combine kernel
+against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -64,27 +65,28 @@ def _run_ffn(moe, cfg, wl, idx):
 
 
 @pytest.mark.parametrize("T,H,E,k,I,E_local,n_sh,I_sh", [
-    # weight-streaming path (T <= 64)
+    # decode batches (T <= 64)
     (16, 256, 8, 2, 512, 8, 0, 0),
     (64, 136, 4, 2, 200, 4, 0, 0),           # K and N not multiples of the tile
     (40, 512, 8, 2, 256, 3, 2, 72),          # remote experts, shared experts over a split K
     (1, 128, 8, 2, 128, 8, 1, 64),
-    # LDS-tiled path
+    # more rows, short K: the mid-sized kernel
     (300, 256, 8, 2, 384, 8, 0, 0),
     (257, 200, 6, 3, 136, 6, 0, 0),          # ragged K, N and M
     (200, 128, 16, 4, 256, 5, 2, 200),       # shared experts over a split K
     (1500, 512, 64, 6, 192, 64, 1, 192),     # many groups, a few rows each
-    # K >= 4096: the half tail tiles (128 x 256), gate/up and down
+    # K >= 4096: 256-row tiles with half tail tiles (128 x 256), gate/up and down
     (500, 4096, 3, 2, 256, 3, 0, 0),
     (500, 256, 3, 2, 4096, 3, 0, 0),
     (500, 4096, 3, 2, 200, 3, 0, 0),         # ... with ragged N
     (500, 200, 3, 2, 4096, 3, 0, 0),
-    # the shared experts' tiles in the routed launch, groups with short
-    # remainders (whole tiles there), short and long K
+    # the shared experts' rows in the routed launch, groups with short
+    # remainders, short and long K (tiles: half tails for gate/up, whole for down)
     (500, 256, 3, 2, 256, 3, 1, 256),
     (500, 4096, 3, 2, 256, 3, 1, 200),
     (500, 200, 3, 2, 4096, 3, 1, 4096),
-    # the tiled kernel's group lookup holds 1, 4 or 16 prefix entries per lane
+    # many groups: gate/up on the mid-sized kernel, one to four batches of
+    # offsets; down past 256 groups on tiles with 16 prefix entries per lane
     (2048, 128, 128, 8, 128, 128, 0, 0),     # 65..256 groups
     (4096, 128, 300, 8, 128, 300, 0, 0),     # 257..1024 groups
     (8192, 64, 1024, 8, 64, 1024, 0, 0),     # the largest group count
@@ -107,8 +109,8 @@ def test_ffn_one_hot_expert_and_empty_experts(moe, T):
 
 
 def test_ffn_group_larger_than_batch(moe):
-    """Duplicate expert ids give one expert more rows than there are tokens:
-    the weight-streaming kernel then walks the rows in several passes."""
+    """Duplicate expert ids give one expert more rows than there are tokens: a
+    decode batch of more than 64 rows in one group."""
     T = 50
     cfg, wl, _ = _case(T, 128, 4, 2, 128, 4)
     idx = np.tile(np.array([[1, 1]], np.int32), (T, 1))
@@ -116,8 +118,8 @@ def test_ffn_group_larger_than_batch(moe):
 
 
 def test_ffn_tile_boundaries(moe):
-    """Groups of 1, 127..129, 255..257 and 511..513 rows: one row, half and
-    whole 256-row m-tiles, and one row past them, side by side in one launch."""
+    """Groups of 1, 127..129, 255..257 and 511..513 rows: one row, whole and half
+    chunks and m-tiles, and one row past them, side by side in one launch."""
     sizes = [1, 127, 128, 129, 255, 256, 257, 511, 512, 513, 65]
     T = sum(sizes)
     cfg, wl, _ = _case(T, 136, len(sizes), 1, 200, len(sizes))
@@ -127,21 +129,21 @@ def test_ffn_tile_boundaries(moe):
 
 @pytest.mark.parametrize("I_sh", [1024, 960])
 def test_ffn_shared_experts_with_or_without_the_routed_launch(moe, I_sh):
-    """4096 tokens and two shared experts: 2 x 1024 shared columns make 16 x 16 = 256
-    gate/up tiles, whole rounds on 256 CUs, so the shared GEMMs keep their own launches;
-    2 x 960 make 240 tiles, which run inside the routed experts' launch."""
+    """4096 tokens and two shared experts of 1024 or 960 columns beside short K:
+    the shared rows in the routed launches (gate/up on the mid-sized kernel, down
+    on whole tiles)."""
     cfg, wl, idx = _case(4096, 128, 16, 2, 128, 16, 2, I_sh)
     _run_ffn(moe, cfg, wl, idx)
 
 
 @pytest.mark.parametrize("T,H,I_sh,which", [
-    (1000, 128, 8192, "up"),       # 4 m-tiles x 64 column tiles: all tiles past the last whole block
-    (2900, 128, 8192, "up"),       # 12 m-tiles: one whole block of 8, then the remainder of 4
-    (1000, 16376, 64, "down"),     # the down projection's 64 column tiles (H = 16376)
-    (2900, 16376, 64, "down"),
+    (1000, 128, 8192, "up"),       # gate/up of short K: on the mid-sized kernel, in the routed launch
+    (2900, 128, 8192, "up"),
+    (1000, 16376, 64, "down"),     # down: 4 m-tiles x 64 column tiles (H = 16376), all past the last whole block
+    (2900, 16376, 64, "down"),     # 12 m-tiles: one whole block of 8, then the remainder of 4
 ])
 def test_ffn_shared_blocked_order_remainder(moe, T, H, I_sh, which):
-    """A launch of the shared experts alone (their tiles fill whole rounds of
+    """Down: a launch of the shared experts alone (their tiles fill whole rounds of
     the 256 compute units) orders its tiles in blocks of 8 m-tiles; these
     shapes have m-tile counts that are not multiples of 8, so the tiles past
     the last whole block take the remainder order.  Every row is checked."""

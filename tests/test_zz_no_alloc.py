@@ -54,9 +54,9 @@ def _both(moe, cfg, wl, w, loc):
 
 
 def test_noalloc_two_calls_match_forward(moe):
-    # a prefill-sized call (tiled GEMMs, shared expert), then a decode-sized
-    # one (weight-streaming GEMMs, chunk-blocked intermediate) on the same
-    # layer: the second finds the first one's data in the scratch array
+    # a prefill-sized call, then a decode-sized one (whose workspace reserves
+    # whole chunks of h rows) on the same layer: the second finds the first
+    # one's data in the scratch array
     base = W.MoeConfig("noalloc", T=300, H=256, E=16, k=4, I=512, S=3, E_local=8, n_shared=1, I_shared=256,
                        local_layout="choice")
     wl_big = W.make_workload(base, seed=11)
