@@ -33,6 +33,25 @@ __device__ __forceinline__ size_t weight_col_offset(const GemmArgs& a, int c) {
   return static_cast<size_t>(q) * a.seg_stride + static_cast<size_t>(c - q * a.kseg);
 }
 
+// Immediate of s_waitcnt (gfx9 layout: vmcnt [3:0] and [15:14], expcnt [6:4],
+// lgkmcnt [11:8]; a field at its maximum does not wait): at most n vector-
+// memory operations in flight, the other counters not waited for.
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+// Workgroup barrier that also fences the compiler: no instruction is moved
+// across it, and memory accesses stay on their side (the hardware waits are
+// the explicit s_waitcnt).
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// 64 lanes x 16 bytes from rs + off[lane] to lds + 16 * lane.
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+}
+
 hipError_t launch_skinny(const Segments& seg, const GemmArgs& a, bool gated, hipStream_t st);
 // Host-side size limits of the weight-streaming kernel (launch_skinny
 // refuses arguments that fail this check).
@@ -55,7 +74,7 @@ constexpr long long kMidMaxBlocks = 0xffffffffll / kMidThreads;  // a grid dimen
 // K from which the kernels count a product as long (see the rules that use it).
 constexpr int kLongK = 4096;
 
-// Largest per-group row count routed to the weight-streaming kernel.
+// Tokens of a decode batch at most (see mid_streams for its kernels).
 constexpr int kSkinnyMaxRows = 64;
 
 }  // namespace moe

@@ -62,18 +62,6 @@ constexpr int kXcds = 8;
 constexpr int kTurn = 8;             // items per turn: a multiple of an XCD's shader engines
 constexpr uint32_t kDead = 0x80000000u;  // past the descriptor's range: reads zeros, no traffic
 
-constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-
-__device__ __forceinline__ void stage_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
-}
-
 struct MidArgs {
   GemmArgs g;   // the routed experts (device offsets)
   GemmArgs sp;  // static rows (shared experts); sp.static_rows == 0: none
@@ -318,7 +306,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     int slot = 0;
     for (int j = 0; j < nst; ++j) {
       __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * LOADS));  // own loads of stage j landed
-      stage_barrier();  // everyone's have, and everyone has read stage j - 1
+      phase_barrier();  // everyone's have, and everyone has read stage j - 1
       issue();          // stage j + D - 1 into the slot of stage j - 1
       const unsigned char* xp = smem + slot * STAGE + wk * XPART;
       const unsigned char* wp = smem + slot * STAGE + NK * XPART + wave * (WB * 32 * ROW);

@@ -1,6 +1,7 @@
-// Expert FFN for decode-sized batches of few, wide experts (the gate/up
-// projection of a Mixtral-shaped layer, see mid_streams): weight streaming.
-// Also takes the decode sizes whose row offsets pass 32 bits.
+// Expert FFN for two kinds of decode-sized batches: small launches of short K,
+// and gate/up projections of many items over mostly hit experts (both in
+// mid_streams).  Also takes the decode sizes, routed and shared, whose offsets
+// within 256 rows pass 32 bits or whose items pass one grid dimension.
 //
 // With at most a few dozen rows per expert the grouped GEMM is bound by
 // reading the active experts' weights from HBM exactly once.  The weights take
@@ -30,11 +31,6 @@ namespace moe {
 namespace {
 
 constexpr uint32_t kInvalidOff = 0x80000000u;  // past the descriptor's range: reads zeros, no traffic
-
-// 64 lanes x 16 bytes from rs + off[lane] to lds + 16 * lane.
-__device__ __forceinline__ void stream_lds16(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
-}
 
 template <bool GATED, int NB, int KP, int KS, int DEPTH>
 __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void skinny_kernel(GemmArgs a) {
@@ -110,9 +106,9 @@ __global__ __launch_bounds__(KP* kWave) __attribute__((amdgpu_waves_per_eu(2, 2)
       for (int b = 0; b < NB; ++b) {
         const uint32_t off = (roff[b][i] + col) | (kok ? 0u : kInvalidOff);
         if (GATED && b == 1)
-          stream_lds16(rs1, dst + b * STEPB + i * 1024, off);
+          load_lds16(rs1, dst + b * STEPB + i * 1024, off);
         else
-          stream_lds16(rs0, dst + b * STEPB + i * 1024, off);
+          load_lds16(rs0, dst + b * STEPB + i * 1024, off);
       }
     }
   };

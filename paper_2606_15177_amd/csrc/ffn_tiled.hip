@@ -90,8 +90,9 @@ constexpr int kMaxGroups = 1024;
 //   long K or no shared rows (kMidMean): DSV3 share gate/up 1.14 at a mean of
 //     16, 1.01 at 28, 1.00 at 38; Mixtral gate/up 1.02 at 32, 0.97 at 50;
 //     Mixtral down 1.01 at 32, 0.93 at 75; Qwen3 down 1.01 at 50, 0.87 at 94;
-//   gate/up with K < kHalfTailK (kMidMeanUp): DSV2-Lite 1.20 at 66, 1.10 at
-//     141, 0.89 at 206; Qwen3 1.13 at 50, 1.05 at 156, 0.95 at 188;
+//   gate/up with K < kHalfTailK (kMidMeanUp, where mid_up_wins agrees): DSV2-
+//     Lite 1.20 at 66, 1.10 at 141, 0.89 at 206; Qwen3 1.13 at 50, 1.05 at 156,
+//     0.95 at 188;
 //   down with shared rows in the launch (kMidMeanShared; whole 256-row tiles
 //     otherwise), by the mean over all weight rows, shared ones included:
 //     DSV2-Lite 1.64 at 85, 1.16 at 303, 0.97 at 363; DSV3 share 1.21 at 91,
@@ -117,23 +118,8 @@ static_assert(kBM == kBN && Stage::RPI * Stage::ROW == 1024, "a load fills 1 KB 
 
 // s_waitcnt immediates (gfx9 layout: vmcnt [3:0] and [15:14], expcnt [6:4],
 // lgkmcnt [11:8]); a field at its maximum does not wait.
-constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 constexpr int kWaitLgkm0 = 15 | (3 << 14) | (7 << 4);
 constexpr int kWaitAll = 0;
-
-// Workgroup barrier that also fences the compiler: no instruction is moved
-// across it, and memory accesses stay on their side (the hardware waits are
-// the explicit s_waitcnt).
-__device__ __forceinline__ void phase_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// 64 lanes x 16 bytes from rsrc + voff[lane] to lds + 16 * lane.
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, uint32_t voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, voff, 0, 0, 0);
-}
 
 // The lane id, recomputed behind a volatile asm: values derived from it are
 // not hoisted out of loops by the compiler and hold no register across them.
@@ -1201,7 +1187,9 @@ bool up_ok(const Segments& seg, const UpArgs& u) {
   return !(u.x_rows && (seg.offsets == nullptr || u.x_row_count <= 0));
 }
 
-// The limits of the kernel a problem runs on (weight streaming or tiled).
+// The limits of the kernels a problem runs on: in decode batches the decode
+// kernel's, which takes whatever the mid-sized one does and more, else the
+// tiles', which the mid-sized one shares.
 // Whether one launch takes two problems or each its own, each problem must
 // pass this, and passing it is all the launchers ask.
 bool gemm_ok(const Segments& seg, const GemmArgs& a) {

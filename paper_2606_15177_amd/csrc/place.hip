@@ -224,11 +224,14 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
-// Scores are never NaN here (a NaN score is replaced by +inf first), so the
-// hardware minimum is exact; of -0.0 and +0.0 it may return either, which the
-// equality test of the tie phase treats alike.  The builtin would first
-// canonicalise both operands (two more instructions of the chain per level),
-// as it cannot know that they are no signalling NaNs.
+// The minimum of two scores.  A score may be a quiet NaN (never a signalling
+// one: it is the result of arithmetic), and the instruction then returns the
+// other operand, so a NaN loses; a minimum over NaNs alone equals no score and
+// an infinite one is not looked for, and both go to the tie path, which counts
+// a NaN as +inf.  Of -0.0 and +0.0 it may return either, which the equality test
+// with the scores treats alike.  The builtin would first canonicalise both
+// operands (two more instructions of the chain per level), as it cannot know
+// that they are no signalling NaNs.
 __device__ __forceinline__ double min_f64(double a, double b) {
   double r;
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
