@@ -7,13 +7,14 @@
 // one group (a chunk) times a block of weight rows.  Groups of up to 64 rows
 // take narrow items of 128 weight rows, larger groups wide ones of 256 (of
 // 128 where a launch has few wide items, which would otherwise run on long
-// after the rest, one to a CU: Mixtral down at 100 tokens 318 -> 223 us,
-// DSV2-Lite down at 200 tokens 97 -> 71 us; with the line at 128, 17 experts of H
-// 2208, I 1064 and a shared one of 1392, 642 tokens, layer 153 us, 116 at 256;
-// at 384 as many layers lose as win).  A wave owns 32-row blocks of the weights (gate/up:
-// 16 gate rows and the 16 up rows of the same columns, which the MFMA's C
-// layout puts into one lane) and all token rows of the chunk.  Dispatched as
-// plain workgroups, two per CU: a persistent grid over 256-row tiles left CUs
+// after the rest: Mixtral down at 100 tokens 318 -> 223 us, DSV2-Lite down at
+// 200 tokens 97 -> 71 us; and up to one per CU where few narrow ones keep them
+// company: 17 experts of H 2208, I 1064 and a shared one of 1392, 642 tokens,
+// layer 153 -> 116 us, while in the DSV3 share of 512 tokens narrow items fill
+// the CUs and the halves cost 1%).  A wave owns 32-row blocks of the weights
+// (gate/up: 16 gate rows and the 16 up rows of the same columns, which the
+// MFMA's C layout puts into one lane) and all token rows of the chunk.
+// Dispatched as plain workgroups, two per CU: a persistent grid over 256-row tiles left CUs
 // idle in its last round and one workgroup per CU waiting at its barriers.
 //
 // Pipeline.  Weights and token rows go by buffer_load_dwordx4 ... lds straight
@@ -24,8 +25,8 @@
 // so that three of 24 KB fit.  Splitting K over the waves as the decode kernel
 // does was slower past 64 tokens (Qwen3 down at 256 tokens 77 us against 90
 // and 141 with 2 and 4 parts: each part needs token rows of its own); a batch
-// with few items halves it (see mid_splits_k).  Also slower: 64-row chunks for hot experts (DSV2-Lite layer, 4096 tokens: 971
-// against 825 us).
+// with few items halves it (see mid_splits_k).  Also slower: 64-row chunks for
+// hot experts (DSV2-Lite layer, 4096 tokens: 971 against 825 us).
 //
 // Order.  Items are numbered per kind; each XCD (workgroup id mod 8) owns a
 // contiguous run of every kind, so an expert's token rows, and the weight
@@ -56,7 +57,9 @@ namespace {
 constexpr int kMidRows = 128;        // token rows of a chunk
 constexpr int kWideRows = 64;        // groups of more rows take wide items
 constexpr int kMidCols = 128;        // weight rows of a narrow item
-constexpr int kFewWide = 256;        // fewer wide items than this (one per CU) take 128 weight rows
+constexpr int kFewWide = 128;        // fewer wide items than this take 128 weight rows: half the CUs' worth
+constexpr int kOneWide = 256;        // ... or fewer than this, one per CU, in a launch of fewer items than
+constexpr int kSlots = 512;          // workgroups fit the chip
 constexpr int kMidLds = 80 * 1024;   // two workgroups per CU
 constexpr int kXcds = 8;
 constexpr int kTurn = 8;             // items per turn: a multiple of an XCD's shader engines
@@ -131,7 +134,8 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
   // items of the shared and of the wide groups where wide items cover `cols` output columns
   auto shared_items = [&](int cols) { return sp_m > 0 ? sp_chunks * col_blocks(sp_m, ma.sp.N, OUT_COLS, cols) : 0; };
   int wide_cols = 2 * FULL_COLS;
-  if (shared_items(wide_cols) + c_wide * ceil_div(ma.g.N, wide_cols) < kFewWide) wide_cols = FULL_COLS;
+  const int heavy = shared_items(wide_cols) + c_wide * ceil_div(ma.g.N, wide_cols);
+  if (heavy < kFewWide || (heavy < kOneWide && heavy + n_narrow < kSlots)) wide_cols = FULL_COLS;
   const int n_shared = shared_items(wide_cols);
   const int wide_blocks = ceil_div(ma.g.N, wide_cols);
   const int n_wide = c_wide * wide_blocks;
