@@ -133,7 +133,7 @@ def stage_work(cfg, R: int, active: int) -> dict:
 # The sources of the layer's kernels: a profile's counters stay valid while
 # these are unchanged (placement and diagnostics kernels do not run in a step).
 LAYER_SOURCES = ("common.h", "ffn_impl.h", "dispatch_impl.h", "route.hip", "permute.hip", "ffn_skinny.hip",
-                 "ffn_tiled.hip", "combine.hip")
+                 "ffn_mid.hip", "ffn_tiled.hip", "combine.hip")
 
 
 def source_digest(names=LAYER_SOURCES) -> str:
@@ -164,8 +164,8 @@ def measured_traffic(stage: str, workload: str):
 STAGE_KERNELS = {
     "route": ("route_kernel<", "stats_kernel"),
     "permute": ("perm_count_kernel", "perm_scan_kernel", "perm_scatter_kernel", "perm_single_kernel"),
-    "ffn_up": ("tiled_kernel<true", "skinny_kernel<true"),
-    "ffn_down": ("tiled_kernel<false", "skinny_kernel<false"),
+    "ffn_up": ("tiled_kernel<true", "mid_kernel<true", "skinny_kernel<true"),
+    "ffn_down": ("tiled_kernel<false", "mid_kernel<false", "skinny_kernel<false"),
     "combine": ("combine_kernel",),
 }
 
