@@ -445,17 +445,18 @@ bool mostly_hit(const Segments& seg) { return 20 * seg.hit_groups >= 19 * seg.gr
 // / 124 us; DSV3 share gate/up, 14 and 24 tokens (400, 610) 120 / 110 and 130
 // / 131 us; a stacked K of the shared experts (DSV2-Lite down, K 2816 among
 // 1408), 12 tokens (730) 38 / 31 us.  Not on long K of gate/up alone with a few
-// more items than half the CUs over mostly hit experts (8 experts of H 4096, 24 and 64 tokens: I
-// 1408, 176 items, 58 / 60 and 64 / 74 us; 4 of H 8192, I 5632, 352 items 227 /
-// 213 and 235 / 244).
+// more items than half the CUs over mostly hit experts (8 experts of H 4096, 24
+// and 64 tokens: I 1408, 176 items, layer 58 / 60 and 64 / 74 us; 4 of H 8192, I
+// 5632, 352 items, 24 tokens 227 / 213).
 // A deeper ring there (six stages in 160 KB, one workgroup per CU) does not
 // pay: Qwen3, 1 token, gate/up 14.6 -> 14.3 us but down 9.0 -> 10.7, and a layer
 // of four 139 -> 147 us, as each kernel waits for whole CUs' LDS.
 bool mid_splits_k(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
   if (seg.max_rows > kWideRows) return false;
   const long long items = narrow_items(seg, a, sh, gated);
-  return items <= 128 || (a.K >= kLongK && items <= (gated ? 400 : 200) && !(gated && !sh && items <= 220 && mostly_hit(seg))) ||
-         (sh && sh->K > a.K && items <= 768);
+  if (items <= 128 || (sh && sh->K > a.K && items <= 768)) return true;
+  if (gated && !sh && items <= 220 && mostly_hit(seg)) return false;
+  return a.K >= kLongK && items <= (gated ? 400 : 200);
 }
 
 long long mid_blocks(const Segments& seg, const GemmArgs& a, const GemmArgs* sh, bool gated) {
